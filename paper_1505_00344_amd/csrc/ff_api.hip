@@ -88,7 +88,6 @@ ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t nsteps) {
     t.steps_per_launch = (int32_t)(nsteps < 4096 ? (nsteps > 0 ? nsteps : 1) : 4096);
     t.block = 256;
     t.particles_per_thread = 1;
-    if (sys->rhs == FF_RHS_HH_RING) t.block = 128;
     // Two particles per thread where a sweep of particles per thread x block
     // on gfx950 found it faster: Wilson-Cowan with the compensated update
     // (3.6%) and Lorenz in FP32 (0.7%).  Plain FP32 Wilson-Cowan is 5% slower

@@ -287,6 +287,118 @@ __device__ __forceinline__ R hh_gate(R a, R b, R x) {
     else return M<R>::fma_(a, R(1) - x, -(b * x));
 }
 
+// One neuron's derivatives from its own five components and the presynaptic
+// neuron's s (spre): the body shared by HHRing (all neurons of a particle in
+// one thread) and RingLane (one neuron per lane).
+template <typename R>
+__device__ __forceinline__ void hh_neuron(const R (&p)[14], R sgl, R invC, const R (&x)[5], R spre, R (&o)[5]) {
+    const R V = x[0], m = x[1], h = x[2], n = x[3], s = x[4];
+    const HHRate<R> q = hh_rates<R>(V, p[12], p[13], sgl);
+    const R gNa = (p[0] * ((m * m) * m)) * h;
+    const R n2 = n * n;
+    const R gK = p[1] * (n2 * n2);
+    const R gS = p[8] * spre;
+    if constexpr (M<R>::kFast) {
+        // the membrane currents accumulated by fma, Iext first
+        R I = M<R>::fma_(p[2], p[5] - V, p[7]);
+        I = M<R>::fma_(gNa, p[3] - V, I);
+        I = M<R>::fma_(gK, p[4] - V, I);
+        I = M<R>::fma_(gS, p[9] - V, I);
+        o[0] = I * invC;
+    } else {
+        const R IL = p[2] * (p[5] - V);
+        o[0] = ((((IL + gNa * (p[3] - V)) + gK * (p[4] - V)) + gS * (p[9] - V)) + p[7]) * invC;
+    }
+    o[1] = hh_gate(q.am, q.bm, m);
+    o[2] = hh_gate(q.ah, q.bh, h);
+    o[3] = hh_gate(q.an, q.bn, n);
+    o[4] = hh_gate(p[10] * q.tv, p[11], s);
+}
+
+// psi'(u) = (expm1(u) - u e^u) / expm1(u)^2, psi'(0) = -1/2.  The
+// numerator is a difference of two terms of size |u| that cancel to
+// -u^2/2, so in fast single precision |u| < 1/2 takes the derivative of
+// the Bernoulli series instead, -1/2 + u/6 - u^3/180 + u^5/5040 -
+// u^7/151200 (the next term, u^9/4790016, is below 4.1e-10 there), and
+// the rest the hardware exponential (cancellation there costs a few
+// ulp).  Both are computed and one is selected.
+template <typename R>
+__device__ __forceinline__ R hh_dpsi(R u) {
+    if constexpr (M<R>::kFast) {
+        const R w = u * u;
+        const R series = M<R>::fma_(
+            u, M<R>::fma_(w, M<R>::fma_(w, M<R>::fma_(w, R(-1.0 / 151200.0), R(1.0 / 5040.0)), R(-1.0 / 180.0)),
+                          R(1.0 / 6.0)),
+            R(-0.5));
+        const R e = M<R>::exp2_(u * R(kLog2e));
+        const R em1 = e - R(1);
+        const R direct = (em1 - u * e) * M<R>::rcp_(em1 * em1);
+        return __builtin_fabsf(u) < R(0.5) ? series : direct;
+    } else if constexpr (kHasKernels<R>) {
+        // u > 350 (V < -3540 mV): psi' is below 1e-149 and expm1(u)^2 would
+        // overflow (a NaN u: the state's V is NaN already)
+        const R uc = __builtin_fmin(u, 350.0);
+        const R em1 = M<double>::expm1_k(uc);
+        const R d = M<double>::div_k(em1 - uc * (em1 + R(1)), em1 * em1);
+        return (u == R(0)) ? R(-0.5) : d;
+    } else {
+        const R em1 = M<R>::expm1_(u);
+        const R d = M<R>::div_(em1 - u * (em1 + R(1)), em1 * em1);
+        return (u == R(0)) ? R(-0.5) : d;
+    }
+}
+
+// One neuron's vector-Jacobian product with its adjoint a: gx += own
+// components, gp += parameters; the return value is what the presynaptic
+// neuron's s receives.
+template <typename R>
+__device__ __forceinline__ R hh_neuron_vjp(const R (&p)[14], R sgl, R invC, const R (&x)[5], R spre, const R (&a)[5],
+                                           R (&gx)[5], R (&gp)[14]) {
+    const R th = p[12], sg = p[13];
+    const R V = x[0], m = x[1], h = x[2], n = x[3], s = x[4];
+    const HHRate<R> q = hh_rates<R>(V, th, sg, sgl);
+    const R um = (V + R(40.0)) * R(-1.0 / 10.0), un = (V + R(55.0)) * R(-1.0 / 10.0);
+    const R dam = hh_dpsi(um) * R(-0.1);
+    const R dbm = q.bm * R(-1.0 / 18.0);
+    const R dah = q.ah * R(-1.0 / 20.0);
+    const R dbh = R(0.1) * q.bh * (R(1) - q.bh);
+    const R dan = R(0.1) * hh_dpsi(un) * R(-0.1);
+    const R dbn = q.bn * R(-1.0 / 80.0);
+    const R dT = sg * q.tv * (R(1) - q.tv);
+    const R m2 = m * m, m3 = m2 * m, n2 = n * n, n3 = n2 * n, n4 = n2 * n2;
+    const R eNa = p[3] - V, eK = p[4] - V, eL = p[5] - V, eS = p[9] - V;
+    const R aV = a[0] * invC;      // membrane adjoint scaled by 1/C
+    const R am_ = a[1], ah_ = a[2], an_ = a[3], as_ = a[4];
+    // d/dV
+    gx[0] += aV * (-p[2] - p[0] * m3 * h - p[1] * n4 - p[8] * spre)
+           + am_ * (dam * (R(1) - m) - dbm * m)
+           + ah_ * (dah * (R(1) - h) - dbh * h)
+           + an_ * (dan * (R(1) - n) - dbn * n)
+           + as_ * (p[10] * dT * (R(1) - s));
+    gx[1] += aV * (R(3) * p[0] * m2 * h * eNa) - am_ * (q.am + q.bm);
+    gx[2] += aV * (p[0] * m3 * eNa) - ah_ * (q.ah + q.bh);
+    gx[3] += aV * (R(4) * p[1] * n3 * eK) - an_ * (q.an + q.bn);
+    gx[4] += -as_ * (p[10] * q.tv + p[11]);
+    // parameters
+    const R dV = (p[2] * eL + p[0] * m3 * h * eNa + p[1] * n4 * eK + p[8] * spre * eS + p[7]) * invC;
+    gp[0] += aV * m3 * h * eNa;
+    gp[1] += aV * n4 * eK;
+    gp[2] += aV * eL;
+    gp[3] += aV * p[0] * m3 * h;
+    gp[4] += aV * p[1] * n4;
+    gp[5] += aV * p[2];
+    gp[6] += -aV * dV;
+    gp[7] += aV;
+    gp[8] += aV * spre * eS;
+    gp[9] += aV * p[8] * spre;
+    const R tq = q.tv * (R(1) - q.tv);
+    gp[10] += as_ * q.tv * (R(1) - s);
+    gp[11] += -as_ * s;
+    gp[12] += as_ * p[10] * (R(1) - s) * (-sg * tq);
+    gp[13] += as_ * p[10] * (R(1) - s) * ((V - th) * tq);
+    return aV * (p[8] * eS);
+}
+
 template <typename R, int N> struct HHRing {
     static constexpr int D = 5 * N, NP = 14, NQ = 1, UNROLL = 1, FUSED_INC = M<R>::kFast;
     static __device__ __forceinline__ void derive(const R (&p)[NP], R (&q)[NQ]) {
@@ -296,111 +408,26 @@ template <typename R, int N> struct HHRing {
         const R invC = M<R>::rcp_(p[6]);
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            const R V = x[5 * j], m = x[5 * j + 1], h = x[5 * j + 2], n = x[5 * j + 3], s = x[5 * j + 4];
-            const R spre = x[5 * ((j + N - 1) % N) + 4];
-            const HHRate<R> q = hh_rates<R>(V, p[12], p[13], qd[0]);
-            const R gNa = (p[0] * ((m * m) * m)) * h;
-            const R n2 = n * n;
-            const R gK = p[1] * (n2 * n2);
-            const R gS = p[8] * spre;
-            if constexpr (M<R>::kFast) {
-                // the membrane currents accumulated by fma, Iext first
-                R I = M<R>::fma_(p[2], p[5] - V, p[7]);
-                I = M<R>::fma_(gNa, p[3] - V, I);
-                I = M<R>::fma_(gK, p[4] - V, I);
-                I = M<R>::fma_(gS, p[9] - V, I);
-                o[5 * j] = I * invC;
-            } else {
-                const R IL = p[2] * (p[5] - V);
-                o[5 * j] = ((((IL + gNa * (p[3] - V)) + gK * (p[4] - V)) + gS * (p[9] - V)) + p[7]) * invC;
-            }
-            o[5 * j + 1] = hh_gate(q.am, q.bm, m);
-            o[5 * j + 2] = hh_gate(q.ah, q.bh, h);
-            o[5 * j + 3] = hh_gate(q.an, q.bn, n);
-            o[5 * j + 4] = hh_gate(p[10] * q.tv, p[11], s);
-        }
-    }
-    // psi'(u) = (expm1(u) - u e^u) / expm1(u)^2, psi'(0) = -1/2.  The
-    // numerator is a difference of two terms of size |u| that cancel to
-    // -u^2/2, so in fast single precision |u| < 1/2 takes the derivative of
-    // the Bernoulli series instead, -1/2 + u/6 - u^3/180 + u^5/5040 -
-    // u^7/151200 (the next term, u^9/4790016, is below 4.1e-10 there), and
-    // the rest the hardware exponential (cancellation there costs a few
-    // ulp).  Both are computed and one is selected.
-    static __device__ __forceinline__ R dpsi(R u) {
-        if constexpr (M<R>::kFast) {
-            const R w = u * u;
-            const R series = M<R>::fma_(
-                u, M<R>::fma_(w, M<R>::fma_(w, M<R>::fma_(w, R(-1.0 / 151200.0), R(1.0 / 5040.0)), R(-1.0 / 180.0)),
-                              R(1.0 / 6.0)),
-                R(-0.5));
-            const R e = M<R>::exp2_(u * R(kLog2e));
-            const R em1 = e - R(1);
-            const R direct = (em1 - u * e) * M<R>::rcp_(em1 * em1);
-            return __builtin_fabsf(u) < R(0.5) ? series : direct;
-        } else if constexpr (kHasKernels<R>) {
-            // u > 350 (V < -3540 mV): psi' is below 1e-149 and expm1(u)^2 would
-            // overflow (a NaN u: the state's V is NaN already)
-            const R uc = __builtin_fmin(u, 350.0);
-            const R em1 = M<double>::expm1_k(uc);
-            const R d = M<double>::div_k(em1 - uc * (em1 + R(1)), em1 * em1);
-            return (u == R(0)) ? R(-0.5) : d;
-        } else {
-            const R em1 = M<R>::expm1_(u);
-            const R d = M<R>::div_(em1 - u * (em1 + R(1)), em1 * em1);
-            return (u == R(0)) ? R(-0.5) : d;
+            const R xj[5] = {x[5 * j], x[5 * j + 1], x[5 * j + 2], x[5 * j + 3], x[5 * j + 4]};
+            R oj[5];
+            hh_neuron<R>(p, qd[0], invC, xj, x[5 * ((j + N - 1) % N) + 4], oj);
+#pragma unroll
+            for (int d = 0; d < 5; ++d) o[5 * j + d] = oj[d];
         }
     }
     static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&qd)[NQ], const R (&x)[D],
                                                const R (&a)[D], R (&gx)[D], R (&gp)[NP]) {
         const R invC = M<R>::rcp_(p[6]);
-        const R th = p[12], sg = p[13];
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            const int o = 5 * j, q5 = 5 * ((j + N - 1) % N);
-            const R V = x[o], m = x[o + 1], h = x[o + 2], n = x[o + 3], s = x[o + 4];
-            const R spre = x[q5 + 4];
-            const HHRate<R> q = hh_rates<R>(V, th, sg, qd[0]);
-            const R um = (V + R(40.0)) * R(-1.0 / 10.0), un = (V + R(55.0)) * R(-1.0 / 10.0);
-            const R dam = dpsi(um) * R(-0.1);
-            const R dbm = q.bm * R(-1.0 / 18.0);
-            const R dah = q.ah * R(-1.0 / 20.0);
-            const R dbh = R(0.1) * q.bh * (R(1) - q.bh);
-            const R dan = R(0.1) * dpsi(un) * R(-0.1);
-            const R dbn = q.bn * R(-1.0 / 80.0);
-            const R dT = sg * q.tv * (R(1) - q.tv);
-            const R m2 = m * m, m3 = m2 * m, n2 = n * n, n3 = n2 * n, n4 = n2 * n2;
-            const R eNa = p[3] - V, eK = p[4] - V, eL = p[5] - V, eS = p[9] - V;
-            const R aV = a[o] * invC;      // membrane adjoint scaled by 1/C
-            const R am_ = a[o + 1], ah_ = a[o + 2], an_ = a[o + 3], as_ = a[o + 4];
-            // d/dV
-            gx[o] += aV * (-p[2] - p[0] * m3 * h - p[1] * n4 - p[8] * spre)
-                   + am_ * (dam * (R(1) - m) - dbm * m)
-                   + ah_ * (dah * (R(1) - h) - dbh * h)
-                   + an_ * (dan * (R(1) - n) - dbn * n)
-                   + as_ * (p[10] * dT * (R(1) - s));
-            gx[o + 1] += aV * (R(3) * p[0] * m2 * h * eNa) - am_ * (q.am + q.bm);
-            gx[o + 2] += aV * (p[0] * m3 * eNa) - ah_ * (q.ah + q.bh);
-            gx[o + 3] += aV * (R(4) * p[1] * n3 * eK) - an_ * (q.an + q.bn);
-            gx[o + 4] += -as_ * (p[10] * q.tv + p[11]);
-            gx[q5 + 4] += aV * (p[8] * eS);
-            // parameters
-            const R dV = (p[2] * eL + p[0] * m3 * h * eNa + p[1] * n4 * eK + p[8] * spre * eS + p[7]) * invC;
-            gp[0] += aV * m3 * h * eNa;
-            gp[1] += aV * n4 * eK;
-            gp[2] += aV * eL;
-            gp[3] += aV * p[0] * m3 * h;
-            gp[4] += aV * p[1] * n4;
-            gp[5] += aV * p[2];
-            gp[6] += -aV * dV;
-            gp[7] += aV;
-            gp[8] += aV * spre * eS;
-            gp[9] += aV * p[8] * spre;
-            const R tq = q.tv * (R(1) - q.tv);
-            gp[10] += as_ * q.tv * (R(1) - s);
-            gp[11] += -as_ * s;
-            gp[12] += as_ * p[10] * (R(1) - s) * (-sg * tq);
-            gp[13] += as_ * p[10] * (R(1) - s) * ((V - th) * tq);
+            const int o = 5 * j, pre = 5 * ((j + N - 1) % N) + 4;
+            const R xj[5] = {x[o], x[o + 1], x[o + 2], x[o + 3], x[o + 4]};
+            const R aj[5] = {a[o], a[o + 1], a[o + 2], a[o + 3], a[o + 4]};
+            R gj[5] = {gx[o], gx[o + 1], gx[o + 2], gx[o + 3], gx[o + 4]};
+            const R gpre = hh_neuron_vjp<R>(p, qd[0], invC, xj, x[pre], aj, gj, gp);
+#pragma unroll
+            for (int d = 0; d < 5; ++d) gx[o + d] = gj[d];
+            gx[pre] += gpre;
         }
     }
 };

@@ -1,0 +1,44 @@
+"""The three-neuron ring with a lane per neuron: 21 particles per wavefront,
+so the edges are multiples of 21 and of a block's 21 * block / 64 particles.
+Launches of one step keep one thread per particle; a run cut into them is the
+reference, bit for bit."""
+import numpy as np
+import pytest
+
+from helpers import api, to_dev, to_host
+from paper_1505_00344_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp32_kahan", "fp64"])
+@pytest.mark.parametrize("n", [1, 20, 21, 22, 63, 64, 83, 84, 85, 257, 1013])
+@pytest.mark.parametrize("block", [64, 256])
+def test_lane_per_neuron_equals_thread_per_particle_bitwise(prec, n, block):
+    A = api()
+    w = I.hh_ring_1m(n=n)
+    e = I.generate(w)
+    ld, off, steps = n + 9, 4, 17
+    dtype = torch.float64 if prec == "fp64" else torch.float32
+    sys_ = A.System("hh_ring", 15, w.params)
+    x0 = np.full((15, ld), 7.0)
+    x0[:, off:off + n] = e.state
+    pp = np.full((2, ld), 0.25)
+    pp[:, off:off + n] = e.pparams * np.linspace(0.5, 1.5, n)
+    out = []
+    for per_launch in (1, steps):
+        st, ppt = to_dev(x0, dtype), to_dev(pp, dtype)
+        comp = torch.full_like(st, 1e-6) if prec == "fp32_kahan" else None
+        A.integrate(sys_, st, 0.01, steps, n=n, offset=off, pparams=ppt, pp_slot=w.pp_slot, comp=comp, prec=prec,
+                    tuning=(per_launch, 1, block))
+        torch.cuda.synchronize()
+        out.append((to_host(st), None if comp is None else to_host(comp)))
+    (a, ac), (b, bc) = out
+    assert not np.array_equal(a, x0)
+    assert np.array_equal(a, b)
+    assert ac is None or np.array_equal(ac, bc)
+    # neighbours in the same rows are untouched
+    for got in (a, b):
+        assert np.all(got[:, :off] == 7.0) and np.all(got[:, off + n:] == 7.0)
