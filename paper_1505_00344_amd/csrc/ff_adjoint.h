@@ -25,10 +25,8 @@ inline AdjArgs make_adj_args(const AdjLaunch& A) {
     a.lam = A.lam;
     a.mu = A.mu;
     a.mu_part = A.mu_part;
-    a.carry = A.carry;
-    a.seg_len = A.seg_len;
-    a.first = A.first;
-    a.last = A.last;
+    a.nsteps = A.nsteps;
+    a.K = A.K;
     return a;
 }
 

@@ -6,17 +6,18 @@
 //   ckpt_c [nseg][D][n]  its Kahan compensation (FF_FP32_KAHAN only)
 //   sub    [nsub][D][n]  sub-checkpoints inside one segment (T steps apart)
 //   sub_c  [nsub][D][n]  their compensation (FF_FP32_KAHAN only)
-//   carry  [NP][n]       per-particle adjoints of every parameter, carried
-//                        from one segment to the next (so the result does
-//                        not depend on K)
-//   mu_part [nblk][16]   FP64 per-block sums of the parameter adjoints
+//   mu_part [nblk][16]   FP64 per-block sums of the parameter adjoints, in a
+//                        region of NP * n values and ceil(n / 256) * 16
+//                        doubles
 // with nseg = ceil(nsteps / K), nsub = ceil(min(K, nsteps) / T) and
-// nblk = ceil(n / 256).
+// nblk = ceil(n / particles per block): 256 particles, or 84 of the ring with
+// a lane per neuron (whose 14 n values alone hold its 16 / 84 n doubles).
 #include <cmath>
 #include <cstring>
 #include <string>
 
 #include "ff_internal.h"
+#include "ff_ring.h"
 
 namespace ff {
 
@@ -31,12 +32,16 @@ int adj_tape_len(const ff_system_s* sys, int prec) {
     return 8;
 }
 
+int adj_per_block(const ff_system_s* sys) {
+    return sys->rhs == FF_RHS_HH_RING && sys->dim == 15 ? ring_per_block<3>(kAdjBlock) : kAdjBlock;
+}
+
 namespace {
 
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct AdjLayout {
-    size_t ckpt, ckpt_c, sub, sub_c, carry, mu_part, total;
+    size_t ckpt, ckpt_c, sub, sub_c, mu_part, total;
     int64_t nseg, nsub, nblk;
 };
 
@@ -48,7 +53,8 @@ AdjLayout adj_layout(const ff_system_s* sys, const ff_batch* b, int64_t nsteps, 
     L.nseg = nsteps > 0 ? (nsteps + K - 1) / K : 0;
     const int64_t seg = nsteps < K ? nsteps : K;
     L.nsub = seg > 0 ? (seg + T - 1) / T : 0;
-    L.nblk = (b->n + kAdjBlock - 1) / kAdjBlock;
+    const int64_t per = adj_per_block(sys);
+    L.nblk = (b->n + per - 1) / per;
     const size_t st = (size_t)sys->dim * (size_t)b->n * esz;
     size_t off = 0;
     L.ckpt = off;
@@ -59,10 +65,9 @@ AdjLayout adj_layout(const ff_system_s* sys, const ff_batch* b, int64_t nsteps, 
     off += al((size_t)L.nsub * st);
     L.sub_c = off;
     if (kahan) off += al((size_t)L.nsub * st);
-    L.carry = off;
-    off += al((size_t)sys->n_params * (size_t)b->n * esz);
     L.mu_part = off;
-    off += al((size_t)L.nblk * kMaxParams * sizeof(double));
+    off += al((size_t)sys->n_params * (size_t)b->n * esz);
+    off += al((size_t)((b->n + kAdjBlock - 1) / kAdjBlock) * kMaxParams * sizeof(double));
     L.total = off;
     return L;
 }
@@ -182,33 +187,28 @@ ff_status ff_adjoint(ff_system_t sys, const ff_batch* b, double dt_signed, int64
         A.h3 = h / 3.0f;
     }
     char* ws = (char*)workspace;
-    const size_t stb = (size_t)sys->dim * (size_t)b->n * esz;
     A.sub = ws + W.sub;
     A.sub_c = b->prec == FF_FP32_KAHAN ? ws + W.sub_c : nullptr;
     A.lam = lambda;
     A.mu = mu;
-    A.mu_part = (double*)(ws + W.mu_part);
-    A.carry = ws + W.carry;
-    for (int64_t s = W.nseg - 1; s >= 0; --s) {
-        A.ckpt = ws + W.ckpt + (size_t)s * stb;
-        A.ckpt_c = b->prec == FF_FP32_KAHAN ? ws + W.ckpt_c + (size_t)s * stb : nullptr;
-        A.seg_len = (nsteps - s * K) < K ? (nsteps - s * K) : K;
-        A.first = s == W.nseg - 1;
-        A.last = s == 0;
-        hipError_t e;
-        switch (sys->rhs) {
-            case FF_RHS_LINEAR: e = launch_adj_linear(sys->dim, A); break;
-            case FF_RHS_LORENZ: e = launch_adj_lorenz(A); break;
-            case FF_RHS_WILSON_COWAN: e = launch_adj_wc(A); break;
-            case FF_RHS_HH_RING: e = launch_adj_hh(sys->dim / 5, A); break;
-            case FF_RHS_EXPR: e = launch_adj_expr(sys, A); break;
-            default: e = hipErrorInvalidValue;
-        }
-        if (e != hipSuccess) return device_fail(e, "ff_adjoint launch");
+    A.mu_part = mu_global ? (double*)(ws + W.mu_part) : nullptr;
+    A.ckpt = ws + W.ckpt;
+    A.ckpt_c = b->prec == FF_FP32_KAHAN ? ws + W.ckpt_c : nullptr;
+    A.nsteps = nsteps;
+    A.K = K;
+    hipError_t e;
+    switch (sys->rhs) {
+        case FF_RHS_LINEAR: e = launch_adj_linear(sys->dim, A); break;
+        case FF_RHS_LORENZ: e = launch_adj_lorenz(A); break;
+        case FF_RHS_WILSON_COWAN: e = launch_adj_wc(A); break;
+        case FF_RHS_HH_RING: e = launch_adj_hh(sys->dim / 5, A); break;
+        case FF_RHS_EXPR: e = launch_adj_expr(sys, A); break;
+        default: e = hipErrorInvalidValue;
     }
+    if (e != hipSuccess) return device_fail(e, "ff_adjoint launch");
     if (mu_global) {
         hipLaunchKernelGGL(k_reduce_mu, dim3(sys->n_params), dim3(256), 0, st, A.mu_part, W.nblk, mu_global);
-        const hipError_t e = hipGetLastError();
+        e = hipGetLastError();
         if (e != hipSuccess) return device_fail(e, "ff_adjoint reduction");
     }
     return FF_OK;

@@ -12,8 +12,10 @@
 //   lam = lam' + (((g4 + g3) + g2) + g1),  mu += sum_i (df/dp)(y_i)^T abar_i.
 // The compensated (Kahan) update is differentiated as exact addition.
 //
-// Memory: one kernel launch per checkpoint segment (the forward pass stored
-// the state every K steps).  Inside a segment each thread
+// Memory: one kernel launch walks every checkpoint segment (the forward pass
+// stored the state every K steps) backwards; the adjoint of the state and the
+// parameter adjoints stay in registers from segment to segment, so results
+// do not depend on K.  Inside a segment each thread
 //   A. replays the segment from its checkpoint, storing its state every T
 //      steps into a sub-checkpoint buffer in HBM (its own slots only), then
 //   B. walks the sub-blocks backwards: re-runs T steps from the
@@ -44,17 +46,14 @@ struct AdjArgs {
     int slot[kMaxPP];
     ParamBlock p;
     double h, h2, h6, h3;
-    const void* ckpt;
+    const void* ckpt;    // [segments][D][n]
     const void* ckpt_c;
-    void* sub;
+    void* sub;           // [ceil(min(K, nsteps) / T)][D][n], one segment's at a time
     void* sub_c;
     void* lam;
     void* mu;
-    double* mu_part;
-    void* carry;  // [NP][n] per-particle parameter adjoints carried between segments
-    int64_t seg_len;
-    int first;    // first segment processed (the last in time): start from zero
-    int last;     // last segment processed (the first in time): write mu, mu_part
+    double* mu_part;     // [blocks][kMaxParams], or null
+    int64_t nsteps, K;
 };
 
 // One reverse step.  LOWREG keeps the stage points y2, y3, y4 out of
@@ -151,15 +150,35 @@ template <class S> struct AdjMinBlocks {
     static constexpr int value = 1;
 };
 
+// Which particle a thread works on, and where its components lie: here one
+// thread per particle.  DT: components of a whole particle; row(d): the row
+// of the thread's d-th component; total(v): v summed over the threads of the
+// particle; leader(): the one that writes what belongs to the particle.
+template <class S> struct ThreadMap {
+    static constexpr int DT = S::D;
+    int64_t i;
+    bool act;
+    __device__ __forceinline__ explicit ThreadMap(int64_t n) {
+        const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+        act = i0 < n;
+        i = act ? i0 : n - 1;  // n >= 1: inactive lanes shadow a valid particle
+    }
+    __device__ __forceinline__ int row(int d) const { return d; }
+    template <typename R> __device__ __forceinline__ R total(R v) const { return v; }
+    __device__ __forceinline__ bool leader() const { return act; }
+    // whether the thread stores sub-checkpoints (a shadow stores the values of
+    // the thread it shadows)
+    __device__ __forceinline__ bool stores() const { return true; }
+};
+
 // CAPTURE (register tape only): the replay of a sub-block also keeps the
 // stage points of every tape state, so that the reverse steps need no right-hand
 // side evaluations of their own (3 * T more values in registers).
-template <class S, typename R, bool KAHAN, int T, bool LOWREG, bool CAPTURE = false>
+template <class S, typename R, bool KAHAN, int T, bool LOWREG, bool CAPTURE = false, class MAP = ThreadMap<S>>
 __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjArgs a) {
-    constexpr int D = S::D, NP = S::NP;
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool act = i0 < a.n;
-    const int64_t i = act ? i0 : a.n - 1;
+    constexpr int D = S::D, DT = MAP::DT, NP = S::NP;
+    const MAP m(a.n);
+    const int64_t i = m.i;
     const int64_t n = a.n;
 
     R p[NP];
@@ -181,34 +200,8 @@ __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjAr
     S::derive(p, qd);
     const R h = R(a.h), h2 = R(a.h2), h6 = R(a.h6), h3 = R(a.h3);
 
-    const R* ck = static_cast<const R*>(a.ckpt);
-    const R* ckc = static_cast<const R*>(a.ckpt_c);
     R* sub = static_cast<R*>(a.sub);
     R* subc = static_cast<R*>(a.sub_c);
-
-    // A. replay the segment, keeping the state every T steps
-    R x[D], c[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        x[d] = ck[d * n + i];
-        c[d] = KAHAN ? ckc[d * n + i] : R(0);
-    }
-    const int64_t L = a.seg_len;
-    const int64_t nsub = (L + T - 1) / T;
-    for (int64_t b = 0; b < nsub; ++b) {
-        R* sb = sub + b * D * n;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            sb[d * n + i] = x[d];
-            // the compensation is only needed to replay steps inside a
-            // sub-block, and a sub-block of one step replays none
-            if (KAHAN && T > 1) subc[b * D * n + d * n + i] = c[d];
-        }
-        if (b + 1 < nsub)
-            for (int t = 0; t < T; ++t) rk4_step<S, R, KAHAN>(p, qd, x, c, h, h2, h6);
-    }
-
-    // B. reverse sweep
     R* stage_lds = nullptr;  // this thread's column of the stage-point store
     if constexpr (LOWREG) {
         __shared__ R stage_store[3 * D * kAdjBlock];
@@ -217,79 +210,103 @@ __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjAr
     R lam[D], gp[NP];
     R* lm = static_cast<R*>(a.lam);
 #pragma unroll
-    for (int d = 0; d < D; ++d) lam[d] = lm[d * a.ld + i];
-    R* carry = static_cast<R*>(a.carry);
+    for (int d = 0; d < D; ++d) lam[d] = lm[m.row(d) * a.ld + i];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) gp[q] = a.first ? R(0) : carry[q * n + i];
-    for (int64_t b = nsub - 1; b >= 0; --b) {
-        const int64_t len = (L - b * T) < T ? (L - b * T) : T;
-        R tape[T][D];
-        R stages[CAPTURE ? T : 1][3][D];  // y2, y3, y4 of every tape state (CAPTURE)
-        R xs[D], cs[D];
+    for (int q = 0; q < NP; ++q) gp[q] = R(0);
+
+    for (int64_t seg = (a.nsteps - 1) / a.K; seg >= 0; --seg) {
+        const int64_t left = a.nsteps - seg * a.K;
+        const int64_t L = left < a.K ? left : a.K;
+        const int64_t nsub = (L + T - 1) / T;
+        // A. replay the segment, keeping the state every T steps
+        {
+            const R* ck = static_cast<const R*>(a.ckpt) + seg * DT * n;
+            const R* ckc = static_cast<const R*>(a.ckpt_c) + seg * DT * n;
+            R x[D], c[D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            xs[d] = sub[b * D * n + d * n + i];
-            cs[d] = (KAHAN && T > 1) ? subc[b * D * n + d * n + i] : R(0);
-            tape[0][d] = xs[d];
+            for (int d = 0; d < D; ++d) {
+                x[d] = ck[m.row(d) * n + i];
+                c[d] = KAHAN ? ckc[m.row(d) * n + i] : R(0);
+            }
+            for (int64_t b = 0; b < nsub; ++b) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    if (m.stores()) sub[(b * DT + m.row(d)) * n + i] = x[d];
+                    // the compensation is only needed to replay steps inside a
+                    // sub-block, and a sub-block of one step replays none
+                    if (KAHAN && T > 1 && m.stores()) subc[(b * DT + m.row(d)) * n + i] = c[d];
+                }
+                if (b + 1 < nsub)
+                    for (int t = 0; t < T; ++t) rk4_step<S, R, KAHAN>(p, qd, x, c, h, h2, h6);
+            }
         }
-        if constexpr (CAPTURE) {
+        // B. reverse sweep
+        for (int64_t b = nsub - 1; b >= 0; --b) {
+            const int64_t len = (L - b * T) < T ? (L - b * T) : T;
+            R tape[T][D];
+            R stages[CAPTURE ? T : 1][3][D];  // y2, y3, y4 of every tape state (CAPTURE)
+            R xs[D], cs[D];
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                if (t + 1 < len) {
-                    rk4_step<S, R, KAHAN, true>(p, qd, xs, cs, h, h2, h6, stages[t]);
+            for (int d = 0; d < D; ++d) {
+                xs[d] = sub[(b * DT + m.row(d)) * n + i];
+                cs[d] = (KAHAN && T > 1) ? subc[(b * DT + m.row(d)) * n + i] : R(0);
+                tape[0][d] = xs[d];
+            }
+            if constexpr (CAPTURE) {
 #pragma unroll
-                    for (int d = 0; d < D; ++d) tape[t + 1][d] = xs[d];
-                } else if (t + 1 == len) {  // the last state: its stage points only
-                    rk4_step<S, R, KAHAN, true, false>(p, qd, xs, cs, h, h2, h6, stages[t]);
+                for (int t = 0; t < T; ++t) {
+                    if (t + 1 < len) {
+                        rk4_step<S, R, KAHAN, true>(p, qd, xs, cs, h, h2, h6, stages[t]);
+#pragma unroll
+                        for (int d = 0; d < D; ++d) tape[t + 1][d] = xs[d];
+                    } else if (t + 1 == len) {  // the last state: its stage points only
+                        rk4_step<S, R, KAHAN, true, false>(p, qd, xs, cs, h, h2, h6, stages[t]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int t = 1; t < T; ++t) {
+                    if (t < len) {
+                        rk4_step<S, R, KAHAN>(p, qd, xs, cs, h, h2, h6);
+#pragma unroll
+                        for (int d = 0; d < D; ++d) tape[t][d] = xs[d];
+                    }
                 }
             }
-        } else {
 #pragma unroll
-            for (int t = 1; t < T; ++t) {
+            for (int t = T - 1; t >= 0; --t) {
                 if (t < len) {
-                    rk4_step<S, R, KAHAN>(p, qd, xs, cs, h, h2, h6);
-#pragma unroll
-                    for (int d = 0; d < D; ++d) tape[t][d] = xs[d];
+                    if constexpr (CAPTURE)
+                        vjp_step<S, R, false, true>(p, qd, tape[t], lam, gp, h, h2, h6, h3, nullptr, stages[t]);
+                    else
+                        vjp_step<S, R, LOWREG>(p, qd, tape[t], lam, gp, h, h2, h6, h3, stage_lds);
                 }
-            }
-        }
-#pragma unroll
-        for (int t = T - 1; t >= 0; --t) {
-            if (t < len) {
-                if constexpr (CAPTURE)
-                    vjp_step<S, R, false, true>(p, qd, tape[t], lam, gp, h, h2, h6, h3, nullptr, stages[t]);
-                else
-                    vjp_step<S, R, LOWREG>(p, qd, tape[t], lam, gp, h, h2, h6, h3, stage_lds);
             }
         }
     }
-    if (act) {
+    if (m.act) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) lm[d * a.ld + i] = lam[d];
-        if (!a.last) {
+        for (int d = 0; d < D; ++d) lm[m.row(d) * a.ld + i] = lam[d];
+    }
+    R* mu = static_cast<R*>(a.mu);
 #pragma unroll
-            for (int q = 0; q < NP; ++q) carry[q * n + i] = gp[q];
-        } else {
-            R* mu = static_cast<R*>(a.mu);
+    for (int k = 0; k < kMaxPP; ++k) {
+        if (k < a.n_pp) {
+            R g = R(0);
 #pragma unroll
-            for (int k = 0; k < kMaxPP; ++k) {
-                if (k < a.n_pp) {
-                    R g = R(0);
-#pragma unroll
-                    for (int q = 0; q < NP; ++q)
-                        if (a.slot[k] == q) g = gp[q];
-                    mu[k * a.ld + i] = g;
-                }
-            }
+            for (int q = 0; q < NP; ++q)
+                if (a.slot[k] == q) g = gp[q];
+            g = m.total(g);
+            if (m.leader()) mu[k * a.ld + i] = g;
         }
     }
     // per-block FP64 sums of every parameter adjoint, in a fixed order
-    if (a.last && a.mu_part) {
+    if (a.mu_part) {
         __shared__ double red[kAdjBlock / 64][kMaxParams];
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-            double v = act ? (double)gp[q] : 0.0;
+            double v = m.act ? (double)gp[q] : 0.0;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
             if (lane == 0) red[wv][q] = v;

@@ -35,23 +35,22 @@ struct RK4Launch {
     RecordArgs* record;      // if set: store every stride-th particle every `every` steps
 };
 
-// Adjoint launch: one reverse segment of a checkpointed run.
+// Adjoint launch: the whole reverse sweep of a checkpointed run.
 struct AdjLaunch {
-    RK4Launch f;         // forward description (pp, n, ld, params, steps; f.h3 below)
+    RK4Launch f;         // forward description (pp, n, ld, params; f.h3 below)
     double h3;           // step/3 rounded to the precision
-    const void* ckpt;    // segment start state, SoA [dim][n]
-    const void* ckpt_c;  // matching Kahan compensation, or null
-    void* sub;           // sub-checkpoint scratch [nsub][dim][n] (+ compensation after it)
+    const void* ckpt;    // segment start states, SoA [segments][dim][n]
+    const void* ckpt_c;  // matching Kahan compensations, or null
+    void* sub;           // sub-checkpoint scratch of one segment [nsub][dim][n]
     void* sub_c;
     void* lam;           // adjoint of the state, SoA [dim][ld], in/out
     void* mu;            // per-particle parameter adjoints, SoA [n_pp][ld]
-    double* mu_part;     // per-block FP64 partial sums of all parameter adjoints [nblk][kMaxParams]
-    void* carry;         // per-particle parameter adjoints between segments [NP][n]
-    int64_t seg_len;     // steps in this segment
-    int first;           // 1 for the first segment processed (last in time)
-    int last;            // 1 for the last segment processed (first in time)
+    double* mu_part;     // per-block FP64 partial sums of all parameter adjoints [nblk][kMaxParams], or null
+    int64_t nsteps, K;   // steps of the run, steps per segment
 };
 
+// Particles per block of the adjoint kernel of `sys` (kAdjBlock threads).
+int adj_per_block(const ff_system_s* sys);
 // Steps held in registers by the adjoint's innermost recompute (per system).
 int adj_tape_len(const ff_system_s* sys, int prec);
 

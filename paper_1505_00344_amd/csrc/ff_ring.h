@@ -100,4 +100,31 @@ __device__ __forceinline__ void ring_tile(const RK4Args& a, int64_t first) {
     }
 }
 
+// The adjoint kernel's view of the same split (ThreadMap is its counterpart
+// for one thread per particle).
+template <int N> struct RingMap {
+    static constexpr int DT = 5 * N;
+    RingWave<N> w;
+    int64_t i;
+    bool act;
+    __device__ __forceinline__ explicit RingMap(int64_t n) {
+        const int64_t i0 = (int64_t)blockIdx.x * ring_per_block<N>(blockDim.x) +
+                           (int64_t)(threadIdx.x >> 6) * RingWave<N>::kPerWave + w.slot;
+        act = w.whole() && i0 < n;
+        i = act ? i0 : n - 1;
+    }
+    __device__ __forceinline__ int row(int d) const { return 5 * w.j + d; }
+    // neuron 0's, then 1's, ... in every lane of the particle
+    template <typename R> __device__ __forceinline__ R total(R v) const {
+        const int first = 4 * ((threadIdx.x & 63) - w.j);
+        R s = lane_read(first, v);
+#pragma unroll
+        for (int k = 1; k < N; ++k) s = s + lane_read(first + 4 * k, v);
+        return s;
+    }
+    __device__ __forceinline__ bool leader() const { return act && w.j == 0; }
+    // the idle last lane has no ring of its own: it must not store
+    __device__ __forceinline__ bool stores() const { return act; }
+};
+
 }  // namespace ff

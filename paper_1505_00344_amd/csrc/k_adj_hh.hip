@@ -1,26 +1,43 @@
 // Discrete-adjoint instantiations: Hodgkin-Huxley rings.  No register tape
-// (every state of a segment is a sub-checkpoint in HBM: 15 doubles per step
-// next to ~4 RK4 steps of exp-heavy arithmetic) and stage points recomputed
-// on demand, so that the 15-dimensional reverse step fits in registers.
+// (every state of a segment is a sub-checkpoint in HBM: 5 doubles per neuron
+// and step next to ~4 RK4 steps of exp-heavy arithmetic).
 #include "ff_adjoint.h"
+#include "ff_ring.h"
 
 namespace ff {
 
 template <typename R> using HH1 = HHRing<R, 1>;
-template <typename R> using HH3 = HHRing<R, 3>;
 
-// The compensated single-precision three-neuron step takes 268 VGPRs, one
-// wave per SIMD; capped at 256 (two waves, 12 registers spilled) its reverse
-// sweep of 1M particles x 2000 steps took 313 instead of 360 ms.  Double
-// precision would spill 184 registers (1198 instead of 960 ms): no cap.
-template <int N> struct AdjMinBlocks<HHRing<float, N>> {
-    static constexpr int value = 2;
-};
+namespace {
+
+// Three neurons: a lane per neuron (ff_ring.h) at every size.  VALU issue
+// bounds it, with 232 VGPRs in single precision (two waves per SIMD) and 256
+// in double (one).  200 steps, K = 50, one thread per particle -> a lane per
+// neuron: 20,011 particles FP64 4.34 -> 1.39 ms, FP32-Kahan 1.84 -> 0.63;
+// 524,288 particles FP64 35.6 -> 30.8 ms, FP32-Kahan 12.4 -> 10.1.  Parking
+// the stage points in LDS (LOWREG), which one thread per particle needs,
+// takes 174 VGPRs in single precision but 12.5 and 38.8 ms.
+template <typename R, bool KAHAN>
+hipError_t launch_ring3_adj(const AdjLaunch& A) {
+    const int per = ring_per_block<3>(kAdjBlock);
+    const int64_t grid = (A.f.n + per - 1) / per;
+    if (grid <= 0) return hipSuccess;
+    hipLaunchKernelGGL((k_adj<RingLane<R, 3>, R, KAHAN, 1, false, false, RingMap<3>>), dim3((unsigned)grid),
+                       dim3(kAdjBlock), 0, A.f.stream, make_adj_args(A));
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_adj_hh(int neurons, const AdjLaunch& A) {
     switch (neurons) {
         case 1: return dispatch_adj<HH1, 1, true>(A);
-        case 3: return dispatch_adj<HH3, 1, true>(A);
+        case 3:
+            switch (A.f.prec) {
+                case FF_FP64: return launch_ring3_adj<double, false>(A);
+                case FF_FP32: return launch_ring3_adj<float, false>(A);
+                case FF_FP32_KAHAN: return launch_ring3_adj<float, true>(A);
+            }
     }
     return hipErrorInvalidValue;
 }

@@ -5,6 +5,7 @@ reference, bit for bit."""
 import numpy as np
 import pytest
 
+import tolerances as tol
 from helpers import api, to_dev, to_host
 from paper_1505_00344_amd import inputs as I
 
@@ -42,3 +43,28 @@ def test_lane_per_neuron_equals_thread_per_particle_bitwise(prec, n, block):
     # neighbours in the same rows are untouched
     for got in (a, b):
         assert np.all(got[:, :off] == 7.0) and np.all(got[:, off + n:] == 7.0)
+
+
+@pytest.mark.parametrize("n,K", [(1, 16), (20, 7), (21, 5), (22, 7), (84, 1), (85, 7), (169, 40)])
+def test_lane_per_neuron_adjoint_matches_oracle(ora, n, K):
+    """Sums over a particle's lanes, ragged last wavefront and block, last
+    segment shorter than K, and the per-block partial sums (more blocks than
+    one per 256 particles)."""
+    A = api()
+    w = I.hh_ring_1m(n=n)
+    e = I.generate(w)
+    steps = 16
+    lamT = np.random.default_rng(3).normal(size=e.state.shape)
+    sys_ = A.System("hh_ring", 15, w.params)
+    x, pp = to_dev(e.state, torch.float64), to_dev(e.pparams, torch.float64)
+    nbytes = A.adjoint_workspace_size(sys_, x, steps, K, pparams=pp, pp_slot=w.pp_slot)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+    A.integrate_checkpointed(sys_, x, 0.01, steps, K, ws, pparams=pp, pp_slot=w.pp_slot)
+    lam, mu = to_dev(lamT, torch.float64), torch.empty_like(pp)
+    mug = torch.empty(len(w.params), dtype=torch.float64, device="cuda:0")
+    A.adjoint(sys_, x, 0.01, steps, K, ws, lam, mu=mu, mu_global=mug, pparams=pp, pp_slot=w.pp_slot)
+    torch.cuda.synchronize()
+    ref = ora.adjoint(ora.HH_RING, w.params, e.state, lamT, 0.01, steps, pp_slot=w.pp_slot, pparams=e.pparams)
+    for got, want in zip((to_host(lam), to_host(mu), to_host(mug)), ref):
+        floor = tol.ADJ_FLOOR * max(np.abs(want).max(), 1.0)
+        assert np.max(np.abs(got - want) / np.maximum(np.abs(want), floor)) <= tol.ADJ_REL
