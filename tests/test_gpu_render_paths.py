@@ -1,0 +1,76 @@
+"""Every route of the particle image at its edges, against the oracle, bit for
+bit: points by global atomics (up to 8192), points packed into 4 and 8 bytes
+and points by index (weights below 1/2, up to 512, beyond), sprites of radius
+1 to 8; 1024, 4096 and 16384 particles per block; ragged images and images of
+one tile; ensembles on one pixel, on two, on a line; one side of the rounding
+of a pixel value and the other."""
+import numpy as np
+import pytest
+
+from helpers import api, to_dev, to_host
+from paper_1505_00344_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+MVP = np.diag([1.0, 1.0, 1.0, 1.0])
+
+
+def ensemble(kind, n):
+    rng = np.random.default_rng(n + 1)
+    x = rng.uniform(-1.1, 1.1, (3, n))
+    if kind == "one_pixel":
+        x[:] = 0.31
+    elif kind == "two_pixels":
+        x[:2] = np.where(np.arange(n) % 2, 0.25, -0.25)
+    elif kind == "line":
+        x[1] = 0.3
+    elif kind == "mostly_one":
+        x[:, rng.uniform(size=n) < 0.9] = -0.123
+    elif kind == "grid":  # sprite centres on pixel corners and centres: many equal distances
+        x[:2] = np.round(x[:2] * 64) / 64
+    x[0, ::97] = np.nan
+    return x
+
+
+def check(ora, x, width, height, radius, weight):
+    A = api()
+    sys_ = A.System("lorenz", 3, I.LORENZ_PARAMS)
+    st = to_dev(x, torch.float64)
+    kw = dict(base=(0.2, 0.5, 1.0), grad=[[0.3, 0, 0], [0, 0.4, 0], [0, 0, -0.5]], weight=weight, radius=radius)
+    spec = ora.render_spec((0, 1, 2), MVP, width, height, **kw)
+    want, wc = ora.render(x, spec)
+    n = x.shape[1]
+    ws = torch.empty(A.render_workspace_size(n, width, height, radius) + 4, dtype=torch.uint8, device="cuda:0")[4:]
+    img, cu = A.render_image(sys_, st, (0, 1, 2), MVP, width, height, workspace=ws, **kw)
+    where = (n, width, height, radius, weight)
+    assert np.array_equal(to_host(img).view(np.uint32), want), where
+    assert int(cu.item()) == wc, where
+    A.render_image(sys_, st, (0, 1, 2), MVP, width, height, img=img, n_culled=cu, accumulate=True, workspace=ws, **kw)
+    assert np.array_equal(to_host(img).view(np.uint32), want + want), where
+    assert int(cu.item()) == 2 * wc, where
+
+
+@pytest.mark.parametrize("n", [1, 8192, 8193, 262145, 1048577])
+@pytest.mark.parametrize("kind", ["uniform", "one_pixel", "two_pixels", "line", "mostly_one"])
+def test_points(ora, n, kind):
+    x = ensemble(kind, n)
+    for width, height in [(640, 361), (65, 33), (64, 32), (1, 1), (1931, 1079)]:
+        for weight in (0.05, 0.498, 0.5, 3.0) if n < 1000000 else (0.05, 0.5):
+            check(ora, x, width, height, 0, weight)
+
+
+@pytest.mark.parametrize("weight", [127.0 / 256, 127.49 / 256, 127.51 / 256, 511.9, 512.1, 1e6, 1.6e7, 0.0])
+def test_point_weights(ora, weight):
+    check(ora, ensemble("uniform", 9001), 300, 200, 0, weight)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "one_pixel", "line", "mostly_one", "grid"])
+@pytest.mark.parametrize("n", [1, 300, 20011, 263000])
+def test_sprites(ora, n, kind):
+    x = ensemble(kind, n)
+    for radius, weight, size in [(1, 0.05, (640, 361)), (2, 1.0, (130, 65)), (4, 40.0, (64, 32)), (8, 0.7, (321, 97)),
+                                 (2, 5000.0, (321, 97))]:
+        if n * (2 * radius + 3) ** 2 < 4e7:
+            check(ora, x, *size, radius, weight)
