@@ -27,6 +27,9 @@ inline AdjArgs make_adj_args(const AdjLaunch& A) {
     a.mu_part = A.mu_part;
     a.nsteps = A.nsteps;
     a.K = A.K;
+    // all of them for the global gradient, else the per-particle ones
+    a.need = A.mu_part ? ~0u : 0u;
+    for (int k = 0; k < A.f.n_pp; ++k) a.need |= 1u << A.f.slot[k];
     return a;
 }
 

@@ -54,6 +54,7 @@ struct AdjArgs {
     void* mu;
     double* mu_part;     // [blocks][kMaxParams], or null
     int64_t nsteps, K;
+    uint32_t need;       // bit k: the adjoint of parameter k is wanted
 };
 
 // One reverse step.  LOWREG keeps the stage points y2, y3, y4 out of
@@ -65,7 +66,7 @@ struct AdjArgs {
 // produced x) instead of being recomputed.
 template <class S, typename R, bool LOWREG, bool HAVE_YS = false>
 __device__ __forceinline__ void vjp_step(const R (&p)[S::NP], const R (&q)[S::NQ], const R (&x)[S::D],
-                                         R (&lam)[S::D], R (&gp)[S::NP], R h, R h2, R h6, R h3,
+                                         R (&lam)[S::D], R (&gp)[S::NP], uint32_t need, R h, R h2, R h6, R h3,
                                          R* lds = nullptr, const R (*given)[S::D] = nullptr) {
     constexpr int D = S::D;
     R ys[3][D];  // y2, y3, y4 when !LOWREG
@@ -104,22 +105,22 @@ __device__ __forceinline__ void vjp_step(const R (&p)[S::NP], const R (&q)[S::NQ
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         a[d] = h6 * lam[d];
-        gs[d] = R(0);
+        gs[d] = R(-0.0);  // the neutral element of addition: x + -0 is x
     }
     // stages 4, 3, 2, 1: the weight that carries g_s into abar_{s-1} is
     // h (stage 4 -> 3) or h/2; the lam' weight of abar_{s-1} is h/3, h/3, h/6
     auto stage = [&](int s) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) g[d] = R(0);
+        for (int d = 0; d < D; ++d) g[d] = R(-0.0);
         if (s == 1) {
-            S::vjp(p, q, x, a, g, gp);
+            S::vjp(p, q, x, a, need, g, gp);
         } else if constexpr (LOWREG) {
             R y[D];
 #pragma unroll
             for (int d = 0; d < D; ++d) y[d] = lds[((s - 2) * D + d) * kAdjBlock];
-            S::vjp(p, q, y, a, g, gp);
+            S::vjp(p, q, y, a, need, g, gp);
         } else {
-            S::vjp(p, q, ys[s - 2], a, g, gp);
+            S::vjp(p, q, ys[s - 2], a, need, g, gp);
         }
         const R wg = (s == 4) ? h : h2;
         const R wl = (s == 2) ? h6 : h3;
@@ -240,7 +241,13 @@ __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjAr
                     for (int t = 0; t < T; ++t) rk4_step<S, R, KAHAN>(p, qd, x, c, h, h2, h6);
             }
         }
-        // B. reverse sweep
+        // B. reverse sweep.  Sub-blocks of one step are a chain of loads, each
+        // of them on its way during the step before it.
+        R ahead[D];
+        if constexpr (T == 1) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) ahead[d] = sub[((nsub - 1) * DT + m.row(d)) * n + i];
+        }
         for (int64_t b = nsub - 1; b >= 0; --b) {
             const int64_t len = (L - b * T) < T ? (L - b * T) : T;
             R tape[T][D];
@@ -248,7 +255,12 @@ __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjAr
             R xs[D], cs[D];
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                xs[d] = sub[(b * DT + m.row(d)) * n + i];
+                if constexpr (T == 1) {
+                    xs[d] = ahead[d];
+                    ahead[d] = sub[((b > 0 ? b - 1 : 0) * DT + m.row(d)) * n + i];
+                } else {
+                    xs[d] = sub[(b * DT + m.row(d)) * n + i];
+                }
                 cs[d] = (KAHAN && T > 1) ? subc[(b * DT + m.row(d)) * n + i] : R(0);
                 tape[0][d] = xs[d];
             }
@@ -277,9 +289,10 @@ __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjAr
             for (int t = T - 1; t >= 0; --t) {
                 if (t < len) {
                     if constexpr (CAPTURE)
-                        vjp_step<S, R, false, true>(p, qd, tape[t], lam, gp, h, h2, h6, h3, nullptr, stages[t]);
+                        vjp_step<S, R, false, true>(p, qd, tape[t], lam, gp, a.need, h, h2, h6, h3, nullptr,
+                                                         stages[t]);
                     else
-                        vjp_step<S, R, LOWREG>(p, qd, tape[t], lam, gp, h, h2, h6, h3, stage_lds);
+                        vjp_step<S, R, LOWREG>(p, qd, tape[t], lam, gp, a.need, h, h2, h6, h3, stage_lds);
                 }
             }
         }

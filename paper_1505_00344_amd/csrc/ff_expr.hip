@@ -400,7 +400,7 @@ std::string expr_struct(const ExprProgram& P, int prec) {
             if (a >= 0 && act[a]) act[i] = 1;
     }
     src += "    static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&q)[NQ], const R (&x)[D], "
-           "const R (&a)[D], R (&gx)[D], R (&gp)[NP]) {\n        (void)p; (void)q; (void)x; (void)a; (void)gx; "
+           "const R (&a)[D], uint32_t, R (&gx)[D], R (&gp)[NP]) {\n        (void)p; (void)q; (void)x; (void)a; (void)gx; "
            "(void)gp;\n";
     for (size_t i = 0; i < N.size(); ++i)
         if (internal((int)i)) src += "        const R v" + std::to_string(i) + " = " + expr_of((int)i, kVjp) + ";\n";

@@ -10,7 +10,10 @@
 //   NQ  number of constants derived from the parameters once per particle,
 //   derive(p, q)                 fill q from p,
 //   f(p, q, x, out)              the right-hand side (autonomous: no t),
-//   vjp(p, q, x, a, gx, gp)      gx += J(x)^T a, gp += (df/dp)^T a.
+//   vjp(p, q, x, a, need, gx, gp)  gx += J(x)^T a, and gp[k] += (df/dp_k)^T a
+//                                for the parameters k whose bit of `need` is
+//                                set (uniform over the launch; the others'
+//                                gp is not read).
 // Parameters live in a per-particle register array p[NP] (global values with
 // per-particle overrides already applied).
 //
@@ -82,13 +85,13 @@ template <typename R, int Dm> struct Linear {
         }
     }
     static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&)[NQ], const R (&x)[D],
-                                               const R (&a)[D], R (&gx)[D], R (&gp)[NP]) {
+                                               const R (&a)[D], uint32_t, R (&gx)[D], R (&gp)[NP]) {
 #pragma unroll
         for (int r = 0; r < D; ++r)
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                gx[c] += p[r * D + c] * a[r];
-                gp[r * D + c] += x[c] * a[r];
+                gx[c] = M<R>::fma_(p[r * D + c], a[r], gx[c]);
+                gp[r * D + c] = M<R>::fma_(x[c], a[r], gp[r * D + c]);
             }
     }
 };
@@ -106,13 +109,15 @@ template <typename R> struct Lorenz {
     // J = [[-s, s, 0], [r - z, -1, -x], [y, x, -b]];  df/dp = diag-like
     // (y - x, x, -z) on (s, r, b).
     static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&)[NQ], const R (&x)[D],
-                                               const R (&a)[D], R (&gx)[D], R (&gp)[NP]) {
-        gx[0] += -p[0] * a[0] + (p[1] - x[2]) * a[1] + x[1] * a[2];
-        gx[1] += p[0] * a[0] - a[1] + x[0] * a[2];
-        gx[2] += -x[0] * a[1] - p[2] * a[2];
-        gp[0] += (x[1] - x[0]) * a[0];
-        gp[1] += x[0] * a[1];
-        gp[2] += -x[2] * a[2];
+                                               const R (&a)[D], uint32_t, R (&gx)[D], R (&gp)[NP]) {
+        gx[0] = M<R>::fma_(-p[0], a[0], M<R>::fma_(p[1] - x[2], a[1], M<R>::fma_(x[1], a[2], gx[0])));
+        gx[1] = M<R>::fma_(p[0], a[0], M<R>::fma_(x[0], a[2], gx[1] - a[1]));
+        gx[2] = M<R>::fma_(-x[0], a[1], M<R>::fma_(-p[2], a[2], gx[2]));
+        // all three always: branches on `need` cost more than the four
+        // operations (4M particles, FP64: 4.74 against 5.24 ms)
+        gp[0] = M<R>::fma_(x[1] - x[0], a[0], gp[0]);
+        gp[1] = M<R>::fma_(x[0], a[1], gp[1]);
+        gp[2] = M<R>::fma_(-x[2], a[2], gp[2]);
     }
 };
 
@@ -166,26 +171,28 @@ template <typename R> struct WilsonCowan {
         o[1] = sI - x[1];
     }
     static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&q)[NQ], const R (&x)[D],
-                                               const R (&a)[D], R (&gx)[D], R (&gp)[NP]) {
-        const R uE = M<R>::fma_(p[0], x[0], M<R>::fma_(-p[1], x[1], p[8]));
-        const R uI = M<R>::fma_(p[2], x[0], M<R>::fma_(-p[3], x[1], p[9]));
+                                               const R (&a)[D], uint32_t need, R (&gx)[D], R (&gp)[NP]) {
         R sE, sI;
         sigmoids(p, q, x, sE, sI);
         const R qE = sE * (R(1) - sE), qI = sI * (R(1) - sI);
         const R dE = p[4] * qE * a[0];   // dS_E/du_E * a_E
         const R dI = p[6] * qI * a[1];
-        gx[0] += p[0] * dE - a[0] + p[2] * dI;
-        gx[1] += -p[1] * dE - p[3] * dI - a[1];
-        gp[0] += dE * x[0];
-        gp[1] += -dE * x[1];
-        gp[2] += dI * x[0];
-        gp[3] += -dI * x[1];
-        gp[4] += (uE - p[5]) * qE * a[0];
-        gp[5] += -dE;
-        gp[6] += (uI - p[7]) * qI * a[1];
-        gp[7] += -dI;
+        gx[0] = M<R>::fma_(p[0], dE, M<R>::fma_(p[2], dI, gx[0] - a[0]));
+        gx[1] = M<R>::fma_(-p[1], dE, M<R>::fma_(-p[3], dI, gx[1] - a[1]));
         gp[8] += dE;
         gp[9] += dI;
+        if (need & 0xffu) {
+            const R uE = M<R>::fma_(p[0], x[0], M<R>::fma_(-p[1], x[1], p[8]));
+            const R uI = M<R>::fma_(p[2], x[0], M<R>::fma_(-p[3], x[1], p[9]));
+            gp[0] = M<R>::fma_(dE, x[0], gp[0]);
+            gp[1] = M<R>::fma_(-dE, x[1], gp[1]);
+            gp[2] = M<R>::fma_(dI, x[0], gp[2]);
+            gp[3] = M<R>::fma_(-dI, x[1], gp[3]);
+            gp[4] = M<R>::fma_((uE - p[5]) * qE, a[0], gp[4]);
+            gp[5] -= dE;
+            gp[6] = M<R>::fma_((uI - p[7]) * qI, a[1], gp[6]);
+            gp[7] -= dI;
+        }
     }
 };
 
@@ -199,8 +206,9 @@ template <typename R> struct WilsonCowan {
 //   bn = 0.125 e^{-(V+65)/80},  T = 1/(1 + e^{-sg (V - th)}),
 //   psi(u) = u / (e^u - 1) with psi(0) = 1 taken by a select (fast single
 //   precision: a Bernoulli series near 0 and the hardware exp2 elsewhere).
+// dm, dn: psi' at the arguments of am and an (double precision, on request).
 template <typename R> struct HHRate {
-    R am, bm, ah, bh, an, bn, tv;
+    R am, bm, ah, bh, an, bn, tv, dm, dn;
 };
 
 // k psi(u) with the fast single-precision functions, given den = (e^u - 1)/k
@@ -231,9 +239,23 @@ __device__ __forceinline__ R hh_psi(R u) {
     }
 }
 
+// psi(u) and psi'(u) from one expm1 and one reciprocal: with w = e^u - 1,
+// psi' = (w - u e^u)/w^2 = (1 - psi e^u)/w.  The difference cancels near 0 to
+// -u/2 with an error of about 2^-53, as w - u e^u does (psi'(0) = -1/2), and
+// nowhere else; (1 - psi)/w - psi would be one operation less but cancels for
+// u << 0, too.
+__device__ __forceinline__ double hh_psi_d(double u, double& d) {
+    const double w = M<double>::expm1_k(__builtin_fmin(u, 700.0));
+    const double r = M<double>::rcp_k(w);
+    const double q0 = u * r;
+    const double q = __builtin_fma(__builtin_fma(-w, q0, u), r, q0);
+    d = (u == 0.0) ? -0.5 : __builtin_fma(-q, w + 1.0, 1.0) * r;
+    return (u == 0.0) ? 1.0 : q;
+}
+
 // Rates of one neuron.  sgl = -sg * log2(e) (derived once per particle) is
-// used by the fast single-precision path only.
-template <typename R>
+// used by the fast single-precision path only; GRAD asks for dm and dn.
+template <typename R, bool GRAD = false>
 __device__ __forceinline__ HHRate<R> hh_rates(R V, R th, R sg, R sgl) {
     const R c10 = R(-1.0 / 10.0);
     const R v65 = V + R(65.0);
@@ -257,8 +279,13 @@ __device__ __forceinline__ HHRate<R> hh_rates(R V, R th, R sg, R sgl) {
         q.bn = M<R>::exp2_(M<R>::fma_(v65, R(-kLog2e / 80.0), R(-3)));
         q.tv = M<R>::rcp_(R(1) + M<R>::exp2_((V - th) * sgl));
     } else {
-        q.am = hh_psi<R>((V + R(40.0)) * c10);
-        q.an = R(0.1) * hh_psi<R>((V + R(55.0)) * c10);
+        if constexpr (GRAD && kHasKernels<R>) {
+            q.am = hh_psi_d((V + R(40.0)) * c10, q.dm);
+            q.an = R(0.1) * hh_psi_d((V + R(55.0)) * c10, q.dn);
+        } else {
+            q.am = hh_psi<R>((V + R(40.0)) * c10);
+            q.an = R(0.1) * hh_psi<R>((V + R(55.0)) * c10);
+        }
         if constexpr (kHasKernels<R>) {
             // the exp kernel overflows to inf and underflows to 0 like the
             // library function for |x| <= 1e15 (|V| <= 1.8e16 mV)
@@ -321,7 +348,8 @@ __device__ __forceinline__ void hh_neuron(const R (&p)[14], R sgl, R invC, const
 // the Bernoulli series instead, -1/2 + u/6 - u^3/180 + u^5/5040 -
 // u^7/151200 (the next term, u^9/4790016, is below 4.1e-10 there), and
 // the rest the hardware exponential (cancellation there costs a few
-// ulp).  Both are computed and one is selected.
+// ulp).  Both are computed and one is selected.  (Double precision takes
+// psi' from hh_psi_d.)
 template <typename R>
 __device__ __forceinline__ R hh_dpsi(R u) {
     if constexpr (M<R>::kFast) {
@@ -334,13 +362,6 @@ __device__ __forceinline__ R hh_dpsi(R u) {
         const R em1 = e - R(1);
         const R direct = (em1 - u * e) * M<R>::rcp_(em1 * em1);
         return __builtin_fabsf(u) < R(0.5) ? series : direct;
-    } else if constexpr (kHasKernels<R>) {
-        // u > 350 (V < -3540 mV): psi' is below 1e-149 and expm1(u)^2 would
-        // overflow (a NaN u: the state's V is NaN already)
-        const R uc = __builtin_fmin(u, 350.0);
-        const R em1 = M<double>::expm1_k(uc);
-        const R d = M<double>::div_k(em1 - uc * (em1 + R(1)), em1 * em1);
-        return (u == R(0)) ? R(-0.5) : d;
     } else {
         const R em1 = M<R>::expm1_(u);
         const R d = M<R>::div_(em1 - u * (em1 + R(1)), em1 * em1);
@@ -349,54 +370,69 @@ __device__ __forceinline__ R hh_dpsi(R u) {
 }
 
 // One neuron's vector-Jacobian product with its adjoint a: gx += own
-// components, gp += parameters; the return value is what the presynaptic
-// neuron's s receives.
+// components, gp += the parameters in `need`; the return value is what the
+// presynaptic neuron's s receives.
 template <typename R>
 __device__ __forceinline__ R hh_neuron_vjp(const R (&p)[14], R sgl, R invC, const R (&x)[5], R spre, const R (&a)[5],
-                                           R (&gx)[5], R (&gp)[14]) {
+                                           uint32_t need, R (&gx)[5], R (&gp)[14]) {
     const R th = p[12], sg = p[13];
     const R V = x[0], m = x[1], h = x[2], n = x[3], s = x[4];
-    const HHRate<R> q = hh_rates<R>(V, th, sg, sgl);
-    const R um = (V + R(40.0)) * R(-1.0 / 10.0), un = (V + R(55.0)) * R(-1.0 / 10.0);
-    const R dam = hh_dpsi(um) * R(-0.1);
+    const HHRate<R> q = hh_rates<R, true>(V, th, sg, sgl);
+    R dpm, dpn;  // psi' at the arguments of am and an
+    if constexpr (kHasKernels<R>) {
+        dpm = q.dm;
+        dpn = q.dn;
+    } else {
+        dpm = hh_dpsi<R>((V + R(40.0)) * R(-1.0 / 10.0));
+        dpn = hh_dpsi<R>((V + R(55.0)) * R(-1.0 / 10.0));
+    }
+    const R dam = dpm * R(-0.1);
     const R dbm = q.bm * R(-1.0 / 18.0);
     const R dah = q.ah * R(-1.0 / 20.0);
     const R dbh = R(0.1) * q.bh * (R(1) - q.bh);
-    const R dan = R(0.1) * hh_dpsi(un) * R(-0.1);
+    const R dan = dpn * R(-0.01);
     const R dbn = q.bn * R(-1.0 / 80.0);
-    const R dT = sg * q.tv * (R(1) - q.tv);
+    const R tq = q.tv * (R(1) - q.tv);
+    const R dT = sg * tq;
     const R m2 = m * m, m3 = m2 * m, n2 = n * n, n3 = n2 * n, n4 = n2 * n2;
-    const R eNa = p[3] - V, eK = p[4] - V, eL = p[5] - V, eS = p[9] - V;
+    const R eNa = p[3] - V, eK = p[4] - V, eS = p[9] - V;
     const R aV = a[0] * invC;      // membrane adjoint scaled by 1/C
     const R am_ = a[1], ah_ = a[2], an_ = a[3], as_ = a[4];
+    const R s1 = R(1) - s;
+    const R aNa = aV * eNa, aK = aV * eK, aS = aV * eS;
+    const R gNa = p[0] * m3, gK = p[1] * n4;  // without h
     // d/dV
-    gx[0] += aV * (-p[2] - p[0] * m3 * h - p[1] * n4 - p[8] * spre)
-           + am_ * (dam * (R(1) - m) - dbm * m)
-           + ah_ * (dah * (R(1) - h) - dbh * h)
-           + an_ * (dan * (R(1) - n) - dbn * n)
-           + as_ * (p[10] * dT * (R(1) - s));
-    gx[1] += aV * (R(3) * p[0] * m2 * h * eNa) - am_ * (q.am + q.bm);
-    gx[2] += aV * (p[0] * m3 * eNa) - ah_ * (q.ah + q.bh);
-    gx[3] += aV * (R(4) * p[1] * n3 * eK) - an_ * (q.an + q.bn);
-    gx[4] += -as_ * (p[10] * q.tv + p[11]);
-    // parameters
-    const R dV = (p[2] * eL + p[0] * m3 * h * eNa + p[1] * n4 * eK + p[8] * spre * eS + p[7]) * invC;
-    gp[0] += aV * m3 * h * eNa;
-    gp[1] += aV * n4 * eK;
-    gp[2] += aV * eL;
-    gp[3] += aV * p[0] * m3 * h;
-    gp[4] += aV * p[1] * n4;
-    gp[5] += aV * p[2];
-    gp[6] += -aV * dV;
+    const R G = M<R>::fma_(p[8], spre, M<R>::fma_(gNa, h, gK + p[2]));
+    R gV = M<R>::fma_(-aV, G, gx[0]);
+    gV = M<R>::fma_(am_, M<R>::fma_(dam, R(1) - m, -(dbm * m)), gV);
+    gV = M<R>::fma_(ah_, M<R>::fma_(dah, R(1) - h, -(dbh * h)), gV);
+    gV = M<R>::fma_(an_, M<R>::fma_(dan, R(1) - n, -(dbn * n)), gV);
+    gx[0] = M<R>::fma_(as_, p[10] * dT * s1, gV);
+    gx[1] = M<R>::fma_(R(3) * p[0] * m2 * h, aNa, M<R>::fma_(-am_, q.am + q.bm, gx[1]));
+    gx[2] = M<R>::fma_(gNa, aNa, M<R>::fma_(-ah_, q.ah + q.bh, gx[2]));
+    gx[3] = M<R>::fma_(R(4) * p[1] * n3, aK, M<R>::fma_(-an_, q.an + q.bn, gx[3]));
+    gx[4] = M<R>::fma_(-as_, M<R>::fma_(p[10], q.tv, p[11]), gx[4]);
+    // parameters: Iext and gsyn, the two that ensembles vary, then the others
     gp[7] += aV;
-    gp[8] += aV * spre * eS;
-    gp[9] += aV * p[8] * spre;
-    const R tq = q.tv * (R(1) - q.tv);
-    gp[10] += as_ * q.tv * (R(1) - s);
-    gp[11] += -as_ * s;
-    gp[12] += as_ * p[10] * (R(1) - s) * (-sg * tq);
-    gp[13] += as_ * p[10] * (R(1) - s) * ((V - th) * tq);
-    return aV * (p[8] * eS);
+    gp[8] = M<R>::fma_(aS, spre, gp[8]);
+    if (need & ~0x180u) {
+        const R eL = p[5] - V, m3h = m3 * h, gNah = gNa * h;
+        gp[0] = M<R>::fma_(m3h, aNa, gp[0]);
+        gp[1] = M<R>::fma_(n4, aK, gp[1]);
+        gp[2] = M<R>::fma_(aV, eL, gp[2]);
+        gp[3] = M<R>::fma_(aV, gNah, gp[3]);
+        gp[4] = M<R>::fma_(aV, gK, gp[4]);
+        gp[5] = M<R>::fma_(aV, p[2], gp[5]);
+        const R dV = M<R>::fma_(p[2], eL, M<R>::fma_(gNah, eNa, M<R>::fma_(gK, eK, M<R>::fma_(p[8] * spre, eS, p[7]))));
+        gp[6] = M<R>::fma_(-aV, dV * invC, gp[6]);
+        gp[9] = M<R>::fma_(aV * p[8], spre, gp[9]);
+        gp[10] = M<R>::fma_(as_ * q.tv, s1, gp[10]);
+        gp[11] = M<R>::fma_(-as_, s, gp[11]);
+        const R aT = as_ * p[10] * s1 * tq;
+        gp[12] = M<R>::fma_(-sg, aT, gp[12]);
+        gp[13] = M<R>::fma_(V - th, aT, gp[13]);
+    }
+    return p[8] * aS;
 }
 
 template <typename R, int N> struct HHRing {
@@ -416,7 +452,7 @@ template <typename R, int N> struct HHRing {
         }
     }
     static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&qd)[NQ], const R (&x)[D],
-                                               const R (&a)[D], R (&gx)[D], R (&gp)[NP]) {
+                                               const R (&a)[D], uint32_t need, R (&gx)[D], R (&gp)[NP]) {
         const R invC = M<R>::rcp_(p[6]);
 #pragma unroll
         for (int j = 0; j < N; ++j) {
@@ -424,7 +460,7 @@ template <typename R, int N> struct HHRing {
             const R xj[5] = {x[o], x[o + 1], x[o + 2], x[o + 3], x[o + 4]};
             const R aj[5] = {a[o], a[o + 1], a[o + 2], a[o + 3], a[o + 4]};
             R gj[5] = {gx[o], gx[o + 1], gx[o + 2], gx[o + 3], gx[o + 4]};
-            const R gpre = hh_neuron_vjp<R>(p, qd[0], invC, xj, x[pre], aj, gj, gp);
+            const R gpre = hh_neuron_vjp<R>(p, qd[0], invC, xj, x[pre], aj, need, gj, gp);
 #pragma unroll
             for (int d = 0; d < 5; ++d) gx[o + d] = gj[d];
             gx[pre] += gpre;

@@ -50,9 +50,10 @@ template <typename R, int N> struct RingLane {
         hh_neuron<R>(p, q[0], M<R>::rcp_(p[6]), x, lane_read(RingWave<N>().prev, x[4]), o);
     }
     static __device__ __forceinline__ void vjp(const R (&p)[NP], const R (&q)[NQ], const R (&x)[D], const R (&a)[D],
-                                               R (&gx)[D], R (&gp)[NP]) {
+                                               uint32_t need, R (&gx)[D], R (&gp)[NP]) {
         const RingWave<N> w;
-        const R gpre = hh_neuron_vjp<R>(p, q[0], M<R>::rcp_(p[6]), x, lane_read(w.prev, x[4]), a, gx, gp);
+        const R gpre = hh_neuron_vjp<R>(p, q[0], M<R>::rcp_(p[6]), x, lane_read(w.prev, x[4]), a, need, gx,
+                                        gp);
         gx[4] += lane_read(w.next, gpre);
     }
 };

@@ -8,15 +8,24 @@ namespace ff {
 
 template <typename R> using HH1 = HHRing<R, 1>;
 
+// One neuron in double precision: two waves per SIMD (256 VGPRs, a few
+// spilled) take 76.6 ms for 4M particles x 200 steps, one wave 82.3; below
+// about 65,536 particles, where there is one wave anyway, 4 % more.
+template <> struct AdjMinBlocks<HHRing<double, 1>> {
+    static constexpr int value = 2;
+};
+
 namespace {
 
 // Three neurons: a lane per neuron (ff_ring.h) at every size.  VALU issue
-// bounds it, with 232 VGPRs in single precision (two waves per SIMD) and 256
-// in double (one).  200 steps, K = 50, one thread per particle -> a lane per
-// neuron: 20,011 particles FP64 4.34 -> 1.39 ms, FP32-Kahan 1.84 -> 0.63;
-// 524,288 particles FP64 35.6 -> 30.8 ms, FP32-Kahan 12.4 -> 10.1.  Parking
-// the stage points in LDS (LOWREG), which one thread per particle needs,
-// takes 174 VGPRs in single precision but 12.5 and 38.8 ms.
+// bounds it, with 240 VGPRs in single precision (two waves per SIMD) and more
+// than 256 in double (one).  200 steps, K = 50, one thread per particle -> a
+// lane per neuron -> psi' shared, loads ahead and the parameter adjoints that are
+// wanted: 20,011 particles FP64 4.34 -> 1.20 -> 1.01 ms, FP32-Kahan 1.84 ->
+// 0.57 -> 0.49; 524,288 particles FP64 35.6 -> 30.7 -> 25.5 ms, FP32-Kahan 12.4
+// -> 10.1 -> 8.1.  Parking the stage points in LDS (LOWREG), which one thread
+// per particle needs, and caps at 256, 168 and 128 VGPRs (spills) are slower:
+// 10.1-11.2 ms in single precision, 32-54 in double.
 template <typename R, bool KAHAN>
 hipError_t launch_ring3_adj(const AdjLaunch& A) {
     const int per = ring_per_block<3>(kAdjBlock);

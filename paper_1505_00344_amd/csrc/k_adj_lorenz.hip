@@ -12,7 +12,7 @@ template <typename R> using Lin4 = Linear<R, 4>;
 // Lorenz keeps the stage points of its tape states (CAPTURE): single
 // precision with the 8-state tape (138 VGPRs), double precision with a
 // 4-state tape (162 VGPRs; with 8 states it would take 258, one wave per
-// SIMD).  Measured on the 8M-particle, 200-step adjoint: FP64 12.0 -> 11.6 ms,
+// SIMD).  Measured with the plain products on the 8M-particle, 200-step adjoint: FP64 12.0 -> 11.6 ms,
 // FP32-Kahan 7.33 -> 7.15 ms, FP32 6.61 -> 6.40 ms, results bitwise unchanged.
 hipError_t launch_adj_lorenz(const AdjLaunch& A) { return dispatch_adj<Lorenz, 8, false, true, 4, true>(A); }
 
