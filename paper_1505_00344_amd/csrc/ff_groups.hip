@@ -21,6 +21,7 @@
 #include <string>
 #include <vector>
 
+#include "ff_ring.h"
 #include "ff_rk4.h"
 
 namespace ff {
@@ -52,8 +53,7 @@ struct GroupTable {
 };
 static_assert(sizeof(GroupTable) <= 3800, "group table must fit the kernel-argument segment");
 
-template <template <typename> class SysT, typename R, bool KAHAN, int PPT>
-__device__ __forceinline__ void run_tile(const GroupTable& tab, const GroupEntry& e, int t) {
+__device__ __forceinline__ RK4Args tile_args(const GroupTable& tab, const GroupEntry& e) {
     RK4Args a;
     a.state = e.state;
     a.comp = e.comp;
@@ -71,7 +71,12 @@ __device__ __forceinline__ void run_tile(const GroupTable& tab, const GroupEntry
     a.ckpt = nullptr;
     a.ckpt_c = nullptr;
     a.ckpt_ld = 0;
-    rk4_tile<SysT<R>, R, KAHAN, PPT>(a, (int64_t)(t - e.tile_begin) * blockDim.x * PPT);
+    return a;
+}
+
+template <template <typename> class SysT, typename R, bool KAHAN, int PPT>
+__device__ __forceinline__ void run_tile(const GroupTable& tab, const GroupEntry& e, int t) {
+    rk4_tile<SysT<R>, R, KAHAN, PPT>(tile_args(tab, e), (int64_t)(t - e.tile_begin) * blockDim.x * PPT);
 }
 
 template <typename R> using HH1 = HHRing<R, 1>;
@@ -81,7 +86,13 @@ template <typename R> using Lin2 = Linear<R, 2>;
 template <typename R> using Lin3 = Linear<R, 3>;
 template <typename R> using Lin4 = Linear<R, 4>;
 
-template <typename R, bool KAHAN, int PPT>
+// LANES: the three-neuron ring takes a lane per neuron (ff_ring.h), which also
+// frees the other systems' tiles of its registers (112 VGPRs instead of 240 for
+// the compensated update).  Mixed batch of 3M Wilson-Cowan, 2M Lorenz and 0.5M
+// ring particles, 200 steps: FP32-Kahan 4.20 -> 3.91 ms, FP32 4.00 -> 3.72; a
+// fiftieth of it: 0.396 -> 0.155 and 0.384 -> 0.230.  Caps at 5, 6 and 8 waves
+// per SIMD were 1-3 % slower on the large batch.
+template <typename R, bool KAHAN, int PPT, bool LANES>
 __global__ void __launch_bounds__(256) k_groups(GroupTable tab, unsigned int* counter) {
     constexpr int PH = PPT > 2 ? 2 : PPT;  // the rings run at most 2 particles per thread
     __shared__ int s_t;
@@ -98,7 +109,13 @@ __global__ void __launch_bounds__(256) k_groups(GroupTable tab, unsigned int* co
             case K_LORENZ: run_tile<Lorenz, R, KAHAN, PPT>(tab, e, t); break;
             case K_WC: run_tile<WilsonCowan, R, KAHAN, PPT>(tab, e, t); break;
             case K_HH1: run_tile<HH1, R, KAHAN, PH>(tab, e, t); break;
-            case K_HH3: run_tile<HH3, R, KAHAN, PH>(tab, e, t); break;
+            case K_HH3:
+                if constexpr (LANES)
+                    ring_tile<R, 3, KAHAN>(tile_args(tab, e),
+                                           (int64_t)(t - e.tile_begin) * ring_per_block<3>(blockDim.x));
+                else
+                    run_tile<HH3, R, KAHAN, PH>(tab, e, t);
+                break;
             case K_LIN1: run_tile<Lin1, R, KAHAN, PPT>(tab, e, t); break;
             case K_LIN2: run_tile<Lin2, R, KAHAN, PPT>(tab, e, t); break;
             case K_LIN3: run_tile<Lin3, R, KAHAN, PPT>(tab, e, t); break;
@@ -132,8 +149,8 @@ double cost_of(int kind) {
 int ppt_of(int kind, int ppt) { return (kind == K_HH1 || kind == K_HH3) ? std::min(ppt, 2) : ppt; }
 
 template <typename R, bool KAHAN>
-hipError_t launch_groups_t(const GroupTable& tab, int ppt, int block, unsigned int* counter, hipStream_t st,
-                           int cus) {
+hipError_t launch_groups_t(const GroupTable& tab, bool lanes, int ppt, int block, unsigned int* counter,
+                           hipStream_t st, int cus) {
     auto go = [&](auto kern) -> hipError_t {
         int per_cu = 0;
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0);
@@ -145,18 +162,18 @@ hipError_t launch_groups_t(const GroupTable& tab, int ppt, int block, unsigned i
         return hipGetLastError();
     };
     switch (ppt) {
-        case 4: return go(k_groups<R, KAHAN, 4>);
-        case 2: return go(k_groups<R, KAHAN, 2>);
-        default: return go(k_groups<R, KAHAN, 1>);
+        case 4: return lanes ? go(k_groups<R, KAHAN, 4, true>) : go(k_groups<R, KAHAN, 4, false>);
+        case 2: return lanes ? go(k_groups<R, KAHAN, 2, true>) : go(k_groups<R, KAHAN, 2, false>);
+        default: return lanes ? go(k_groups<R, KAHAN, 1, true>) : go(k_groups<R, KAHAN, 1, false>);
     }
 }
 
-hipError_t launch_groups(int prec, const GroupTable& tab, int ppt, int block, unsigned int* counter,
+hipError_t launch_groups(int prec, const GroupTable& tab, bool lanes, int ppt, int block, unsigned int* counter,
                          hipStream_t st, int cus) {
     switch (prec) {
-        case FF_FP64: return launch_groups_t<double, false>(tab, ppt, block, counter, st, cus);
-        case FF_FP32: return launch_groups_t<float, false>(tab, ppt, block, counter, st, cus);
-        case FF_FP32_KAHAN: return launch_groups_t<float, true>(tab, ppt, block, counter, st, cus);
+        case FF_FP64: return launch_groups_t<double, false>(tab, lanes, ppt, block, counter, st, cus);
+        case FF_FP32: return launch_groups_t<float, false>(tab, lanes, ppt, block, counter, st, cus);
+        case FF_FP32_KAHAN: return launch_groups_t<float, true>(tab, lanes, ppt, block, counter, st, cus);
     }
     return hipErrorInvalidValue;
 }
@@ -195,9 +212,22 @@ ff_status device_info(unsigned int** counter, int* cus, bool need_counter, hipSt
 struct Prepared {
     std::vector<GroupTable> tables;
     int prec = -1;
+    bool lanes = true;
 };
 
-ff_status prepare(const ff_group* groups, int32_t n_groups, const ff_tuning& t, Prepared* out) {
+// A lane per neuron from eight steps a launch on: below, HBM bounds the ring,
+// and reads its lanes' rows less well.  In double precision the lanes gain
+// nothing once one thread per particle fills the chip (500,000 rings in the
+// mixed batch: 12.04 -> 12.24 ms; 100,000: 2.90 -> 2.48).
+bool ring_lanes(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t) {
+    if (std::min<int64_t>(nsteps, t.steps_per_launch) < 8) return false;
+    int64_t rings = 0;
+    for (int i = 0; i < n_groups; ++i)
+        if (groups[i].b.prec == FF_FP64 && kind_of(groups[i].sys) == K_HH3) rings += groups[i].b.n;
+    return rings < 4 * 65536;
+}
+
+ff_status prepare(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t, Prepared* out) {
     if (!groups && n_groups > 0) return fail(FF_E_INVALID, "groups is NULL");
     if (n_groups < 0) return fail(FF_E_INVALID, "n_groups < 0");
     struct Item {
@@ -219,6 +249,7 @@ ff_status prepare(const ff_group* groups, int32_t n_groups, const ff_tuning& t, 
         const int k = kind_of(g.sys);
         items.push_back({i, k, cost_of(k)});
     }
+    out->lanes = ring_lanes(groups, n_groups, nsteps, t);
     std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.cost > b.cost; });
     GroupTable tab;
     std::memset(&tab, 0, sizeof tab);
@@ -257,7 +288,8 @@ ff_status prepare(const ff_group* groups, int32_t n_groups, const ff_tuning& t, 
         e.h = L.h;
         e.h2 = L.h2;
         e.h6 = L.h6;
-        const int64_t per_tile = (int64_t)t.block * e.ppt;
+        const int64_t per_tile =
+            it.kind == K_HH3 && out->lanes ? ring_per_block<3>(t.block) : (int64_t)t.block * e.ppt;
         const int64_t tiles = (g.b.n + per_tile - 1) / per_tile;
         if ((int64_t)tab.ntiles + tiles > 0x7fffffffLL) return fail(FF_E_UNSUPPORTED, "too many tiles");
         e.tile_begin = tab.ntiles;
@@ -273,7 +305,7 @@ ff_status run_prepared(Prepared& P, int64_t nsteps, const ff_tuning& t, unsigned
     for (GroupTable& tab : P.tables) {
         for (int64_t done = 0; done < nsteps;) {
             tab.steps = std::min<int64_t>(t.steps_per_launch, nsteps - done);
-            const hipError_t e = launch_groups(P.prec, tab, t.particles_per_thread, t.block, counter, st, cus);
+            const hipError_t e = launch_groups(P.prec, tab, P.lanes, t.particles_per_thread, t.block, counter, st, cus);
             if (e != hipSuccess) return device_fail(e, "ff_integrate_groups launch");
             done += tab.steps;
         }
@@ -376,7 +408,7 @@ ff_status ff_integrate_groups(const ff_group* groups, int32_t n_groups, int64_t 
         t.block = 256;
     }
     Prepared P;
-    if (ff_status s = prepare(groups, n_groups, t, &P)) return s;
+    if (ff_status s = prepare(groups, n_groups, nsteps, t, &P)) return s;
     if (!tuning) {
         // the groups are valid now: take ff_autotune's choice for this list
         bool hit = false;
@@ -386,7 +418,7 @@ ff_status ff_integrate_groups(const ff_group* groups, int32_t n_groups, int64_t 
         }
         if (hit) {
             P = Prepared();
-            if (ff_status s = prepare(groups, n_groups, t, &P)) return s;
+            if (ff_status s = prepare(groups, n_groups, nsteps, t, &P)) return s;
         }
     }
     if (nsteps == 0 || P.tables.empty()) return FF_OK;
@@ -406,7 +438,7 @@ ff_status ff_autotune(const ff_group* groups, int32_t n_groups, int64_t nsteps, 
     ff_tuning probe{1, 1, 256};
     {
         Prepared P;
-        if (ff_status s = prepare(groups, n_groups, probe, &P)) return s;
+        if (ff_status s = prepare(groups, n_groups, nsteps, probe, &P)) return s;
         if (P.tables.empty()) {
             *out = ff_tuning{(int32_t)std::min<int64_t>(nsteps, 500), 1, 256};
             return FF_OK;
@@ -462,7 +494,7 @@ ff_status ff_autotune(const ff_group* groups, int32_t n_groups, int64_t nsteps, 
     // one candidate: a warm-up, then one timed run of tune_steps steps
     auto trial = [&](const ff_tuning& t, float* ms) -> ff_status {
         Prepared P;
-        if (ff_status s = prepare(copy.data(), n_groups, t, &P)) return s;
+        if (ff_status s = prepare(copy.data(), n_groups, tune_steps, t, &P)) return s;
         if (ff_status s = run_prepared(P, std::min<int64_t>(t.steps_per_launch, tune_steps), t, counter, cus, st))
             return s;
         if (hipError_t e = hipEventRecord(ev[0], st)) return device_fail(e, "ff_autotune: hipEventRecord");

@@ -68,3 +68,34 @@ def test_lane_per_neuron_adjoint_matches_oracle(ora, n, K):
     for got, want in zip((to_host(lam), to_host(mu), to_host(mug)), ref):
         floor = tol.ADJ_FLOOR * max(np.abs(want).max(), 1.0)
         assert np.max(np.abs(got - want) / np.maximum(np.abs(want), floor)) <= tol.ADJ_REL
+
+
+@pytest.mark.parametrize("prec", ["fp32_kahan", "fp64"])
+@pytest.mark.parametrize("tuning", [(3, 1, 256), (17, 1, 256), (17, 2, 64), (9, 4, 192)])
+def test_ring_groups_equal_separate_calls(prec, tuning):
+    """The batch kernel's two splits of the ring (launches of fewer than eight
+    steps, and more), next to another system's group."""
+    A = api()
+    dtype = torch.float64 if prec == "fp64" else torch.float32
+    hh, lz = A.System("hh_ring", 15, I.HH_PARAMS), A.System("lorenz", 3, I.LORENZ_PARAMS)
+    sizes = [1, 20, 22, 85, 300]
+    n = sum(sizes)
+    x0 = I.generate(I.hh_ring_1m(n=n)).state
+    y0 = I.random_state(1, 3, 77, I.LORENZ_BOX)
+    out = []
+    for batched in (True, False):
+        x, y = to_dev(x0, dtype), to_dev(y0, dtype)
+        cx, cy = (torch.zeros_like(x), torch.zeros_like(y)) if prec == "fp32_kahan" else (None, None)
+        specs, off = [(lz, A.make_batch(y, None, None, (), cy, prec, 0), 0.005)], 0
+        for m in sizes:
+            specs.append((hh, A.make_batch(x, m, None, (), cx, prec, off), 0.01))
+            off += m
+        if batched:
+            A.integrate_groups(A.make_groups(specs), 20, tuning=tuning)
+        else:
+            A.integrate(hh, x, 0.01, 20, comp=cx, prec=prec, tuning=(1, 1, 256))
+            A.integrate(lz, y, 0.005, 20, comp=cy, prec=prec, tuning=(1, 1, 256))
+        torch.cuda.synchronize()
+        out.append([to_host(v) for v in (x, y)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
