@@ -137,7 +137,7 @@ ff_status ff_integrate_checkpointed(ff_system_t sys, const ff_batch* b, double d
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = default_tuning(sys, b->prec, K);
+    const ff_tuning t = default_tuning(sys, b->prec, b->n, K);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     const size_t st = (size_t)sys->dim * (size_t)b->n * prec_size(b->prec);
     char* ws = (char*)workspace;
@@ -176,7 +176,7 @@ ff_status ff_adjoint(ff_system_t sys, const ff_batch* b, double dt_signed, int64
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprAdjoint)) return s;
     }
-    const ff_tuning t = default_tuning(sys, b->prec, K);
+    const ff_tuning t = default_tuning(sys, b->prec, b->n, K);
     AdjLaunch A;
     std::memset(&A, 0, sizeof A);
     A.f = make_launch(sys, b, dt_signed, &t, st);

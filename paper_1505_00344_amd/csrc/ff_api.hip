@@ -83,17 +83,22 @@ ff_status check_tuning(const ff_system_s* sys, const ff_tuning* t) {
     return FF_OK;
 }
 
-ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t nsteps) {
+ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t nsteps) {
     ff_tuning t;
     t.steps_per_launch = (int32_t)(nsteps < 4096 ? (nsteps > 0 ? nsteps : 1) : 4096);
     t.block = 256;
     t.particles_per_thread = 1;
-    // Two particles per thread where a sweep of particles per thread x block
-    // on gfx950 found it faster: Wilson-Cowan with the compensated update
-    // (3.6%) and Lorenz in FP32 (0.7%).  Plain FP32 Wilson-Cowan is 5% slower
-    // with two; FP64 and the Hodgkin-Huxley ring gain nothing.
-    if ((sys->rhs == FF_RHS_WILSON_COWAN && prec == FF_FP32_KAHAN) ||
-        (sys->rhs == FF_RHS_LORENZ && prec != FF_FP64))
+    // Two particles per thread where a sweep on gfx950 found it faster:
+    // Wilson-Cowan with the compensated update, whose transcendentals leave
+    // the second particle's arithmetic room (200 steps of 4M: 1703 -> 1649 us).
+    // Two take whole rounds of 131,072 particles, a wave on each SIMD, where
+    // one takes rounds of 65,536 that cost 1/0.968 of a half, so the smaller
+    // rounds win where they are fewer (4,096 to 65,536 particles: 40 against
+    // 67 us; 400,003: 199 against 218), and in the first two anyway.  The
+    // others gain nothing from two (Lorenz 8M in single precision: within
+    // 0.3 %; 65,536: 26 against 38 us; plain Wilson-Cowan is 5 % slower).
+    if (sys->rhs == FF_RHS_WILSON_COWAN && prec == FF_FP32_KAHAN && n > 131072 &&
+        0.968 * 2.0 * (double)((n + 131071) / 131072) < (double)((n + 65535) / 65536))
         t.particles_per_thread = 2;
     return t;
 }
@@ -223,7 +228,7 @@ ff_status ff_integrate(ff_system_t sys, const ff_batch* b, double dt_signed, int
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, nsteps);
+    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     for (int64_t done = 0; done < nsteps;) {
         L.steps = nsteps - done < t.steps_per_launch ? nsteps - done : t.steps_per_launch;
@@ -311,7 +316,7 @@ extern "C" ff_status ff_integrate_reset(ff_system_t sys, const ff_batch* b, doub
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, nsteps);
+    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     L.reset = &r;
     return run_steps(sys, L, nsteps, t.steps_per_launch, "ff_integrate_reset launch");
@@ -336,7 +341,7 @@ extern "C" ff_status ff_integrate_record(ff_system_t sys, const ff_batch* b, dou
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, nsteps);
+    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     RecordArgs rc;
     rc.out = out;
