@@ -87,6 +87,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_fns = {}  # the library's functions, looked up once
 
 
 class FirefliesError(RuntimeError):
@@ -119,10 +120,12 @@ def lib(required_symbols=None):
 
 def call(name: str, *args) -> None:
     """Call an ff_* function and raise FirefliesError on a non-OK status."""
-    L = lib()
-    fn = getattr(L, name, None)
+    fn = _fns.get(name)
     if fn is None:
-        raise RuntimeError(f"libfireflies.so does not export {name}")
+        fn = getattr(lib(), name, None)
+        if fn is None:
+            raise RuntimeError(f"libfireflies.so does not export {name}")
+        _fns[name] = fn
     st = fn(*args)
     if st != FF_OK:
-        raise FirefliesError(st, name, L.ff_last_error().decode(errors="replace"))
+        raise FirefliesError(st, name, _lib.ff_last_error().decode(errors="replace"))

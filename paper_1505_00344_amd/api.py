@@ -22,9 +22,18 @@ RHS = {"linear": FF_RHS_LINEAR, "lorenz": FF_RHS_LORENZ, "wilson_cowan": FF_RHS_
 PREC = {"fp32": FF_FP32, "fp32_kahan": FF_FP32_KAHAN, "fp64": FF_FP64}
 
 
+# torch.cuda.current_stream() builds a stream object (2.6 us a call); a display
+# loop's call takes about 8 us in all, so the handle is asked for directly
+# where this torch has the call.
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream if hasattr(s, "cuda_stream") else int(s)
+    if stream is None:
+        if _current_raw_stream is not None and torch.cuda.is_initialized():
+            return _current_raw_stream(torch._C._cuda_getDevice())
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -46,12 +55,13 @@ def _check_out(t: torch.Tensor, name: str, shape, dtypes, min_numel: bool = Fals
 def _check_gpu(like: Optional[torch.Tensor], **tensors) -> None:
     """Every tensor whose memory the library reads or writes must live on a GPU
     (the one of the state, ``like``): a host pointer would reach a kernel."""
+    device = -1 if like is None else like.get_device()  # an index: quicker to compare than devices
     for name, t in tensors.items():
         if t is None:
             continue
         if not t.is_cuda:
             raise ValueError(f"{name} must be a GPU tensor, not on {t.device}")
-        if like is not None and t.device != like.device:
+        if device >= 0 and t.get_device() != device:
             raise ValueError(f"{name} is on {t.device} but the state is on {like.device}")
 
 
