@@ -371,8 +371,10 @@ __global__ void __launch_bounds__(kSort) k_hist_split(Segments sg, int64_t per, 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Scratch of the two-pass path: per block of C particles its sorted indices
-// and the starts of its tiles, and the list of over-full tiles' parts.  C = 1024 K: one block for each of the 256 CUs
-// while the ensemble is too small to fill them otherwise.
+// and the starts of its tiles, and the list of over-full tiles' parts.  C =
+// 1024 K: one or two blocks for each of the 256 CUs while the ensemble is too
+// small to fill them with 16 particles a thread (1.5M particles: K = 16 37 us,
+// K = 4 30; 4M: K = 4 43, K = 16 38).
 struct WsLayout {
     int K, nblk;
     size_t sorted, starts, items, n_items, total;
@@ -383,7 +385,8 @@ WsLayout layout(int64_t n, int nx, int ny) {
     const int64_t nbins = (int64_t)nx * ny;
     if (nbins <= (int64_t)kSmallBins) return L;
     const Tiling t = tiling(nx, ny);
-    L.K = t.ntiles > 1024 ? 16 : n <= 256 * (int64_t)kSort ? 1 : n <= 256 * 4 * (int64_t)kSort ? 4 : 16;
+    const int64_t full = 256 * (int64_t)kSort;
+    L.K = t.ntiles > 1024 ? 16 : n <= full ? 1 : n <= 8 * full ? 4 : n <= 16 * full ? 8 : 16;
     const int64_t C = (int64_t)kSort * L.K;
     L.nblk = (int)((n + C - 1) / C);
     L.sorted = 0;
@@ -454,6 +457,7 @@ hipError_t run_hist(const R* ax, const R* ay, int64_t n, const Geom& g, uint32_t
     const int64_t clear = accumulate ? 0 : nbins;
     if (L.K == 1) launch_partition<R, 1>(ax, ay, n, g, t, L, ws, hist, clear, st);
     else if (L.K == 4) launch_partition<R, 4>(ax, ay, n, g, t, L, ws, hist, clear, st);
+    else if (L.K == 8) launch_partition<R, 8>(ax, ay, n, g, t, L, ws, hist, clear, st);
     else launch_partition<R, 16>(ax, ay, n, g, t, L, ws, hist, clear, st);
     if (hipError_t e = hipGetLastError()) return e;
     switch (t.bits) {

@@ -38,8 +38,8 @@
 //      same code) has a margin in LDS on the right and below for what reaches
 //      into its neighbours; the partition has cleared the image.
 // HBM traffic per point: read 3 coordinates, write and read 4 or 8 B; plus the
-// image once.  8,388,608 settled Lorenz particles at 1920 x 1080: 410 -> 106 us
-// (partition 63, points 25, their parts 21), of which reading the coordinates
+// image once.  8,388,608 settled Lorenz particles at 1920 x 1080: 410 -> 99 us
+// (partition 55, points 25, their parts 21), of which reading the coordinates
 // and writing the image at the 4.6 TB/s of a large copy are 27; the partition
 // is bound by its double-precision projection and the LDS counting.  500,009
 // sprites of radius 2 at 1280 x 720: 137 -> 60 us (partition 12, list 5, draw
@@ -66,7 +66,6 @@ struct RenderArgs {
     double base[3], grad[9], origin[3];
     double weight;
     int radius;
-    uint32_t grads;  // bit 3k + j: the term grad[3k + j] (a_j - origin_j) may be other than 0
 };
 
 constexpr int kRTileW = 64, kRTileH = 32;
@@ -126,10 +125,8 @@ __device__ __forceinline__ Point project(R a0, R a1, R a2, const RenderArgs& r) 
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         double v = r.base[k];
-        // a zero gradient adds 0 (a kept particle's coordinates are finite)
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
-            if (r.grads >> (3 * k + j) & 1u) v += r.grad[3 * k + j] * (a[j] - r.origin[j]);
+        for (int j = 0; j < 3; ++j) v += r.grad[3 * k + j] * (a[j] - r.origin[j]);
         P.rgb[k] = fmin(fmax(v, 0.0), 1.0);
     }
     return P;
@@ -912,12 +909,7 @@ ff_status ff_render_image(ff_system_t sys, const ff_batch* b, const ff_render* r
         a.base[k] = r->base[k];
         a.origin[k] = r->origin[k];
     }
-    a.grads = 0;
-    for (int k = 0; k < 9; ++k) {
-        a.grad[k] = r->grad[k];
-        // 0 (a - origin) is 0 unless the difference could overflow
-        if (!(r->grad[k] == 0.0 && std::fabs(r->origin[k % 3]) <= 1e290)) a.grads |= 1u << k;
-    }
+    for (int k = 0; k < 9; ++k) a.grad[k] = r->grad[k];
     a.weight = r->weight;
     a.radius = r->radius;
     const RLayout L = rlayout(b->n, r->width, r->height, r->radius, r->weight, b->prec == FF_FP64);
