@@ -83,7 +83,7 @@ ff_status check_tuning(const ff_system_s* sys, const ff_tuning* t) {
     return FF_OK;
 }
 
-ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t nsteps) {
+ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t nsteps, bool plain) {
     ff_tuning t;
     t.steps_per_launch = (int32_t)(nsteps < 4096 ? (nsteps > 0 ? nsteps : 1) : 4096);
     t.block = 256;
@@ -96,8 +96,11 @@ ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t ns
     // rounds win where they are fewer (4,096 to 65,536 particles: 40 against
     // 67 us; 400,003: 199 against 218), and in the first two anyway.  The
     // others gain nothing from two (Lorenz 8M in single precision: within
-    // 0.3 %; 65,536: 26 against 38 us; plain Wilson-Cowan is 5 % slower).
-    if (sys->rhs == FF_RHS_WILSON_COWAN && prec == FF_FP32_KAHAN && n > 131072 &&
+    // 0.3 %; 65,536: 26 against 38 us; plain Wilson-Cowan is 5 % slower), and
+    // neither does it with the reset rule or recording (not `plain`), whose
+    // wave-wide votes and stores two particles repeat (2M, 200 steps: 943
+    // against 962 us, every step recorded 845 against 902).
+    if (plain && sys->rhs == FF_RHS_WILSON_COWAN && prec == FF_FP32_KAHAN && n > 131072 &&
         0.968 * 2.0 * (double)((n + 131071) / 131072) < (double)((n + 65535) / 65536))
         t.particles_per_thread = 2;
     return t;
@@ -228,7 +231,7 @@ ff_status ff_integrate(ff_system_t sys, const ff_batch* b, double dt_signed, int
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps);
+    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps, true);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     for (int64_t done = 0; done < nsteps;) {
         L.steps = nsteps - done < t.steps_per_launch ? nsteps - done : t.steps_per_launch;
@@ -316,7 +319,7 @@ extern "C" ff_status ff_integrate_reset(ff_system_t sys, const ff_batch* b, doub
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps);
+    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps, false);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     L.reset = &r;
     return run_steps(sys, L, nsteps, t.steps_per_launch, "ff_integrate_reset launch");
@@ -341,7 +344,7 @@ extern "C" ff_status ff_integrate_record(ff_system_t sys, const ff_batch* b, dou
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps);
+    const ff_tuning t = tuning ? *tuning : default_tuning(sys, b->prec, b->n, nsteps, false);
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     RecordArgs rc;
     rc.out = out;

@@ -113,6 +113,6 @@ hipError_t launch_rk4_expr(const ff_system_s* sys, const RK4Launch& L);
 hipError_t launch_adj_expr(const ff_system_s* sys, const AdjLaunch& A);
 void expr_destroy(ExprProgram* p);
 // Default particles per thread / block for n particles of a system in a precision.
-ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t nsteps);
+ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t nsteps, bool plain = true);
 
 }  // namespace ff
