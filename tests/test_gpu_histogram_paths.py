@@ -55,6 +55,18 @@ def test_every_route_is_exact(ora, n, kind):
         assert int(d.item()) == 2 * wd
 
 
+@pytest.mark.gpu
+def test_few_particles_clear_a_large_grid(ora):
+    """More of the grid than the particles' blocks clear, held by something else before."""
+    A = api()
+    x = ensemble("uniform", 8193)
+    want, _ = ora.histogram(x, 0, 1, (0.0, 1.0), (0.0, 1.0), 5000, 3000)
+    h = torch.full((3000, 5000), -1, dtype=torch.int32, device="cuda:0")
+    A.project_histogram(A.System("lorenz", 3, I.LORENZ_PARAMS), to_dev(x, torch.float64), 0, 1, (0.0, 1.0),
+                        (0.0, 1.0), 5000, 3000, hist=h)
+    assert np.array_equal(to_host(h).view(np.uint32), want)
+
+
 def test_workspace_size_is_unchanged():
     """6 bytes per particle, 4 per 16384-bin tile and 4096 particles, and the
     tile totals: callers may have sized their workspaces with it."""

@@ -74,3 +74,18 @@ def test_sprites(ora, n, kind):
                                  (2, 5000.0, (321, 97))]:
         if n * (2 * radius + 3) ** 2 < 4e7:
             check(ora, x, *size, radius, weight)
+
+
+@pytest.mark.parametrize("n", [1, 1024, 1025])
+def test_few_sprites_clear_a_large_image(ora, n):
+    """More of the image than the particles' blocks clear, held by something else before."""
+    A = api()
+    x = ensemble("uniform", n)
+    size = (1931, 1079)
+    img = torch.full((size[1], size[0], 3), -1, dtype=torch.int32, device="cuda:0")
+    for prec in (torch.float64, torch.float32):
+        st = to_dev(x, prec)
+        want, _ = ora.render(to_host(st).astype(np.float64), ora.render_spec((0, 1, 2), MVP, *size, weight=0.7, radius=1))
+        A.render_image(A.System("lorenz", 3, I.LORENZ_PARAMS), st, (0, 1, 2), MVP, *size, weight=0.7, radius=1,
+                       img=img.fill_(-1))
+        assert np.array_equal(to_host(img).view(np.uint32), want), prec
