@@ -216,15 +216,26 @@ struct Prepared {
 };
 
 // A lane per neuron from eight steps a launch on: below, HBM bounds the ring,
-// and reads its lanes' rows less well.  In double precision the lanes gain
+// and reads its lanes' rows less well.  Between two rounds of lanes and four of
+// threads (43,008 and 262,144 rings) they need as many rounds as threads do
+// and win that back later (60,000 rings, FP32: 8 steps 27.7 -> 31.6 us, 16
+// steps 42.4 -> 44.8, 32 steps 71.2 -> 70.5; 40,000: 25.9 -> 24.5, 39.7 ->
+// 33.3; 300,000: 92.5 -> 89.1, 160 -> 145).  In double precision the lanes gain
 // nothing once one thread per particle fills the chip (500,000 rings in the
-// mixed batch: 12.04 -> 12.24 ms; 100,000: 2.90 -> 2.48).
+// mixed batch: 12.04 -> 12.24 ms; 100,000: 2.90 -> 2.48).  Without rings the
+// other systems' tiles are faster at the lower occupancy (300,000
+// Wilson-Cowan and 400,000 Lorenz particles, 100 steps, FP32: 120 against 140
+// us).
 bool ring_lanes(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t) {
-    if (std::min<int64_t>(nsteps, t.steps_per_launch) < 8) return false;
+    const int64_t steps = std::min<int64_t>(nsteps, t.steps_per_launch);
     int64_t rings = 0;
-    for (int i = 0; i < n_groups; ++i)
-        if (groups[i].b.prec == FF_FP64 && kind_of(groups[i].sys) == K_HH3) rings += groups[i].b.n;
-    return rings < 4 * 65536;
+    bool f64 = false;
+    for (int i = 0; i < n_groups; ++i) {
+        if (kind_of(groups[i].sys) == K_HH3) rings += groups[i].b.n;
+        f64 = f64 || groups[i].b.prec == FF_FP64;
+    }
+    if (rings == 0 || (f64 && rings >= 4 * 65536)) return false;
+    return steps >= (rings > 2 * 21504 && rings <= 4 * 65536 ? 32 : 8);
 }
 
 ff_status prepare(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t, Prepared* out) {
