@@ -137,7 +137,13 @@ ff_status ff_integrate_checkpointed(ff_system_t sys, const ff_batch* b, double d
     if (sys->expr) {
         if (ff_status s = expr_prepare(sys, b->prec, kExprForward)) return s;
     }
-    const ff_tuning t = default_tuning(sys, b->prec, b->n, K);
+    ff_tuning t = default_tuning(sys, b->prec, b->n, K);
+    // A checkpoint at every step leaves little but loads and stores, of which
+    // two particles per thread keep more in flight (1M Lorenz particles, seven
+    // steps: FP32-Kahan 92 against 105 us, FP32 46 against 48; 140,001: 31.4
+    // against 30).
+    if (sys->rhs == FF_RHS_LORENZ && b->prec != FF_FP64 && K == 1 && b->n >= (int64_t)1 << 19)
+        t.particles_per_thread = 2;
     RK4Launch L = make_launch(sys, b, dt_signed, &t, (hipStream_t)stream);
     const size_t st = (size_t)sys->dim * (size_t)b->n * prec_size(b->prec);
     char* ws = (char*)workspace;
