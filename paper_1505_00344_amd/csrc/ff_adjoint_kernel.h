@@ -167,9 +167,6 @@ template <class S> struct ThreadMap {
     __device__ __forceinline__ int row(int d) const { return d; }
     template <typename R> __device__ __forceinline__ R total(R v) const { return v; }
     __device__ __forceinline__ bool leader() const { return act; }
-    // whether the thread stores sub-checkpoints (a shadow stores the values of
-    // the thread it shadows)
-    __device__ __forceinline__ bool stores() const { return true; }
 };
 
 // CAPTURE (register tape only): the replay of a sub-block also keeps the
@@ -230,12 +227,16 @@ __global__ void __launch_bounds__(kAdjBlock, AdjMinBlocks<S>::value) k_adj(AdjAr
                 c[d] = KAHAN ? ckc[m.row(d) * n + i] : R(0);
             }
             for (int64_t b = 0; b < nsub; ++b) {
+                // The slots are used again by every segment and the waves of a
+                // block run apart, so only the particle's own thread may store:
+                // a shadow's segment can be another than the owner's.  What a
+                // shadow reads back is whatever is there, and is not used.
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    if (m.stores()) sub[(b * DT + m.row(d)) * n + i] = x[d];
+                    if (m.act) sub[(b * DT + m.row(d)) * n + i] = x[d];
                     // the compensation is only needed to replay steps inside a
                     // sub-block, and a sub-block of one step replays none
-                    if (KAHAN && T > 1 && m.stores()) subc[(b * DT + m.row(d)) * n + i] = c[d];
+                    if (KAHAN && T > 1 && m.act) subc[(b * DT + m.row(d)) * n + i] = c[d];
                 }
                 if (b + 1 < nsub)
                     for (int t = 0; t < T; ++t) rk4_step<S, R, KAHAN>(p, qd, x, c, h, h2, h6);

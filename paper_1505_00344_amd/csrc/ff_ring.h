@@ -124,8 +124,6 @@ template <int N> struct RingMap {
         return s;
     }
     __device__ __forceinline__ bool leader() const { return act && w.j == 0; }
-    // the idle last lane has no ring of its own: it must not store
-    __device__ __forceinline__ bool stores() const { return act; }
 };
 
 }  // namespace ff
