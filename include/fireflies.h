@@ -280,7 +280,9 @@ ff_status ff_integrate_record(ff_system_t sys, const ff_batch* b, double dt_sign
  * 0 <= iy < ny (NaN fails), and then hist[iy*nx + ix] += 1; otherwise
  * *n_dropped += 1.  Counts are exact.  hist: device uint32 [ny][nx];
  * n_dropped: device uint64 or NULL (not counted); accumulate == 0 first sets
- * hist (and *n_dropped) to zero.  workspace: device scratch of at least
+ * hist (and *n_dropped) to zero, otherwise the call adds to them atomically
+ * (overlapping calls on several streams, each with its own workspace, may add
+ * to one grid).  workspace: device scratch of at least
  * ff_histogram_workspace_size() bytes, or NULL to use library-owned scratch
  * (one buffer per device, allocated on first use and grown when needed: calls
  * that use it concurrently on different streams of one device race, and
@@ -333,7 +335,9 @@ ff_status ff_project_histogram_noalloc(ff_system_t sys, const ff_batch* b, int32
  * and independent of particle order; a channel's sum wraps modulo 2^32 (after
  * 2^24 full-weight, full-colour hits of one pixel), so weight should keep the
  * densest pixel below that; n_culled: device uint64 or NULL; accumulate == 0
- * clears both first.  width * height <= 2^28, radius <= 64.
+ * clears both first, otherwise the call adds to them atomically (overlapping
+ * calls on several streams, each with its own workspace, may add to one
+ * image).  width * height <= 2^28, radius <= 64.
  * workspace: device scratch of at least ff_render_workspace_size() bytes (0
  * when the call needs none: sprites of radius > 8, images of more than 4096
  * tiles of 64 x 32 pixels, or more than 2^29 particles), or NULL to use

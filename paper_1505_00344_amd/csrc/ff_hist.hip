@@ -332,7 +332,11 @@ __global__ void __launch_bounds__(kSort) k_hist_accum(Segments sg, int64_t n, in
         for (int b = threadIdx.x; b < sg.nblk; b += kSort) kept += sg.starts[(int64_t)b * (nt + 1) + nt];
         if (kept) atomicAdd((unsigned long long*)&s_sum, kept);
         __syncthreads();
-        if (threadIdx.x == 0) *dropped = (accumulate ? *dropped : 0ull) + ((unsigned long long)n - s_sum);
+        if (threadIdx.x == 0) {
+            const unsigned long long drops = (unsigned long long)n - s_sum;
+            if (accumulate) atomicAdd(dropped, drops);
+            else *dropped = drops;
+        }
         return;
     }
     const int64_t total = (int64_t)tile_total(sg, nt, t, 0, sg.nblk, &s_sum);
@@ -346,7 +350,9 @@ __global__ void __launch_bounds__(kSort) k_hist_accum(Segments sg, int64_t n, in
         return;
     }
     gather_tile<BITS, 16>(s, sg, nt, t, 0, sg.nblk);
-    if (accumulate) merge_tile<BITS>(s, g, tl, t, hist, [](uint32_t* d, uint32_t v) { *d += v; });
+    // what is added to the caller's grid is added atomically: calls on several
+    // streams may add to one grid
+    if (accumulate) merge_tile<BITS>(s, g, tl, t, hist, [](uint32_t* d, uint32_t v) { atomicAdd(d, v); });
     else merge_tile<BITS>(s, g, tl, t, hist, [](uint32_t* d, uint32_t v) { *d = v; });
 }
 

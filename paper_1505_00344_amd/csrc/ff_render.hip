@@ -30,9 +30,10 @@
 //      sprite is its particle's three coordinates (its index in double
 //      precision), in the tile of its first pixel
 //   2. points: one block owns a tile, gathers the tile's runs from all
-//      segments, adds them up in LDS and stores the tile, the only time the
-//      image is written; a tile that holds more than a block's share is listed
-//      instead.  Sprites: every tile is listed, in parts
+//      segments, adds them up in LDS and stores the tile (or adds it to an
+//      accumulated image, atomically), the only time the image is written; a
+//      tile that holds more than a block's share is listed instead.  Sprites:
+//      every tile is listed, in parts
 //   3. the listed parts, added up in LDS and merged with one global atomic per
 //      non-zero pixel and channel.  A tile of sprites (projected again by the
 //      same code) has a margin in LDS on the right and below for what reaches
@@ -627,7 +628,10 @@ __device__ __forceinline__ void count_culled(const RSegments<P>& g, int nt, bool
     for (int b = threadIdx.x; b < g.nblk; b += blockDim.x) mine += g.starts[(int64_t)b * (nt + 2) + nt + 1];
     if (mine) atomicAdd(s_sum, mine);
     __syncthreads();
-    if (threadIdx.x == 0) *culled = (accumulate ? *culled : 0ull) + *s_sum;
+    if (threadIdx.x == 0) {
+        if (accumulate) atomicAdd(culled, (unsigned long long)*s_sum);
+        else *culled = *s_sum;
+    }
 }
 
 // Lists tile t in parts of about `per` entries; called by the whole block.
@@ -675,8 +679,9 @@ __global__ void __launch_bounds__(kRSort) k_points_accum(RSegments<P> g, RTiles 
     __syncthreads();
     if (total) gather_points<P, 16>(s, g, T.nt, t, 0, g.nblk);
     __syncthreads();
-    // no other block has this tile
-    if (T.accumulate) each_pixel(s, T, t, 0, r, [](uint32_t* d, uint32_t v) { if (v) *d += v; });
+    // no other block has this tile, but calls on other streams may add to the
+    // same image
+    if (T.accumulate) each_pixel(s, T, t, 0, r, [](uint32_t* d, uint32_t v) { if (v) atomicAdd(d, v); });
     else each_pixel(s, T, t, 0, r, [](uint32_t* d, uint32_t v) { *d = v; });
 }
 
