@@ -1,6 +1,7 @@
 // ff_api.hip — C ABI: system handles, validation, errors, and ff_integrate.
 #include <cfloat>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 #include <new>
 #include <string>
@@ -286,7 +287,9 @@ ff_status fill_reset(const ff_system_s* sys, const ff_batch* b, const ff_reset* 
         r->wf[d] = (float)r->wd[d];
         r->lof[d] = (float)reset->box_lo[d];
     }
-    r->max_age = reset->max_age;
+    // No int32 age exceeds INT32_MAX: a limit from there on is none, and the
+    // kernel's sums of a limit, an age and a step stay far inside 64 bits.
+    r->max_age = reset->max_age >= INT32_MAX ? -1 : reset->max_age;
     r->seed = reset->seed;
     r->id_offset = reset->id_offset;
     r->age = reset->age;

@@ -115,7 +115,7 @@ struct ResetArgs {
     float blf[kMaxDim], bhf[kMaxDim];   // smallest float >= blo, largest float <= bhi
     double wd[kMaxDim], lod[kMaxDim];   // box width and low end (double)
     float wf[kMaxDim], lof[kMaxDim];    // the same rounded to float
-    int64_t max_age;
+    int64_t max_age;                    // below INT32_MAX; negative: no limit
     uint64_t seed, id_offset;
     int32_t* age;
     uint32_t* nres;

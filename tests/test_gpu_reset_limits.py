@@ -1,0 +1,46 @@
+"""The reset rule's age limit at the ends of its 64-bit range and of the 32-bit
+ages, against the oracle, whose rule is `age > max_age` in 64 bits."""
+import numpy as np
+import pytest
+
+from helpers import api, to_dev, to_host
+from paper_1505_00344_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+BOUNDS = [(-40.0, 40.0), (-60.0, 60.0), (-10.0, 80.0)]
+TOP = 2 ** 31 - 1
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp32_kahan"])
+@pytest.mark.parametrize("max_age", [2 ** 63 - 1, 2 ** 63 - 2, 2 ** 32 + 7, TOP, TOP - 1, TOP - 100, 0, -1, -2 ** 63])
+@pytest.mark.parametrize("record", [False, True])
+def test_age_limits(ora, prec, max_age, record):
+    A = api()
+    n, steps = 700, 60
+    dtype = torch.float64 if prec == "fp64" else torch.float32
+    rng = np.random.default_rng(7)
+    x0 = np.array([rng.uniform(-45, 45, n), rng.uniform(-65, 65, n), rng.uniform(-15, 85, n)])
+    x0 = x0 if prec == "fp64" else x0.astype(np.float32)
+    # up to what sixty steps reach without passing the largest int32
+    ages = np.resize(np.array([0, 1, -5, -2 ** 31, TOP - 60, TOP - 110, 1000], dtype=np.int64), n).astype(np.int32)
+    x, age, nres = to_dev(x0, dtype), to_dev(ages, torch.int32), torch.zeros(n, dtype=torch.int32, device="cuda:0")
+    comp = torch.zeros_like(x) if prec == "fp32_kahan" else None
+    sys_ = A.System("lorenz", 3, I.LORENZ_PARAMS)
+    # backward, where particles leave the bounds; in launches of 25 steps, across which ages are carried
+    rule = dict(bounds=BOUNDS, box=I.LORENZ_BOX, age=age, n_resets=nres, max_age=max_age, seed=11)
+    kw = dict(comp=comp, prec=prec, tuning=(25, 1, 256))
+    if record:
+        A.integrate_record(sys_, x, -0.005, steps, 10, 1, reset=rule, **kw)
+    else:
+        A.integrate_reset(sys_, x, -0.005, steps, **rule, **kw)
+    torch.cuda.synchronize()
+    want = ora.rk4_reset(ora.LORENZ, I.LORENZ_PARAMS, x0, -0.005, steps, BOUNDS, I.LORENZ_BOX, max_age=max_age, seed=11,
+                         age=ages, prec=prec)
+    assert want[3].any()
+    assert np.array_equal(to_host(x), want[0])
+    assert comp is None or np.array_equal(to_host(comp), want[1])
+    assert np.array_equal(to_host(age), want[2])
+    assert np.array_equal(to_host(nres).view(np.uint32), want[3])
