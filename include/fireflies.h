@@ -113,7 +113,8 @@ typedef struct {
 
 /* Launch shape.  steps_per_launch: RK4 steps fused per kernel launch (the
  * state stays in registers between them); particles_per_thread: 1, 2 or 4
- * (the Hodgkin-Huxley rings are limited to 2; larger requests are clamped);
+ * (the Hodgkin-Huxley rings are limited to 2, larger requests are clamped; at
+ * 1 a three-neuron ring may take three neighbouring lanes, a neuron each);
  * block: threads per block, a multiple of 64 in [64, 256].  Results are
  * bitwise independent of all three. */
 typedef struct {

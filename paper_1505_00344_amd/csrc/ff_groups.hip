@@ -86,12 +86,13 @@ template <typename R> using Lin2 = Linear<R, 2>;
 template <typename R> using Lin3 = Linear<R, 3>;
 template <typename R> using Lin4 = Linear<R, 4>;
 
-// LANES: the three-neuron ring takes a lane per neuron (ff_ring.h), which also
-// frees the other systems' tiles of its registers (112 VGPRs instead of 240 for
-// the compensated update).  Mixed batch of 3M Wilson-Cowan, 2M Lorenz and 0.5M
-// ring particles, 200 steps: FP32-Kahan 4.20 -> 3.91 ms, FP32 4.00 -> 3.72; a
-// fiftieth of it: 0.396 -> 0.155 and 0.384 -> 0.230.  Caps at 5, 6 and 8 waves
-// per SIMD were 1-3 % slower on the large batch.
+// LANES (one particle per thread only): the three-neuron ring takes a lane per
+// neuron (ff_ring.h), which also frees the other systems' tiles of its
+// registers (112 VGPRs instead of 240 for the compensated update).  Mixed batch
+// of 3M Wilson-Cowan, 2M Lorenz and 0.5M ring particles, 200 steps: FP32-Kahan
+// 4.20 -> 3.91 ms, FP32 4.00 -> 3.72; a fiftieth of it: 0.396 -> 0.155 and
+// 0.384 -> 0.230.  Caps at 5, 6 and 8 waves per SIMD were 1-3 % slower on the
+// large batch.
 template <typename R, bool KAHAN, int PPT, bool LANES>
 __global__ void __launch_bounds__(256) k_groups(GroupTable tab, unsigned int* counter) {
     constexpr int PH = PPT > 2 ? 2 : PPT;  // the rings run at most 2 particles per thread
@@ -162,8 +163,8 @@ hipError_t launch_groups_t(const GroupTable& tab, bool lanes, int ppt, int block
         return hipGetLastError();
     };
     switch (ppt) {
-        case 4: return lanes ? go(k_groups<R, KAHAN, 4, true>) : go(k_groups<R, KAHAN, 4, false>);
-        case 2: return lanes ? go(k_groups<R, KAHAN, 2, true>) : go(k_groups<R, KAHAN, 2, false>);
+        case 4: return go(k_groups<R, KAHAN, 4, false>);
+        case 2: return go(k_groups<R, KAHAN, 2, false>);
         default: return lanes ? go(k_groups<R, KAHAN, 1, true>) : go(k_groups<R, KAHAN, 1, false>);
     }
 }
@@ -227,6 +228,7 @@ struct Prepared {
 // Wilson-Cowan and 400,000 Lorenz particles, 100 steps, FP32: 120 against 140
 // us).
 bool ring_lanes(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t) {
+    if (t.particles_per_thread > 1) return false;  // the caller's tuning, or ff_autotune's, asks for more
     const int64_t steps = std::min<int64_t>(nsteps, t.steps_per_launch);
     int64_t rings = 0;
     bool f64 = false;

@@ -43,7 +43,8 @@ hipError_t launch_ring3(const RK4Launch& L) {
 // FP32: 38 -> 56 us); the steps win that back from the sixth on (65,536
 // particles or fewer: the second).
 bool lane_per_neuron(const RK4Launch& L) {
-    if (L.reset || L.record || L.n > (int64_t)1 << 30) return false;
+    // two particles per thread are what the caller's tuning asks for
+    if (L.ppt > 1 || L.reset || L.record || L.n > (int64_t)1 << 30) return false;
     if (L.steps < (L.n <= 65536 ? 2 : 8)) return false;
     const int64_t threads = (L.n + 65535) / 65536, lanes = (L.n + 21503) / 21504;
     return (double)lanes * (L.prec == FF_FP64 ? 0.337 : 0.31) < (double)threads;
@@ -52,8 +53,9 @@ bool lane_per_neuron(const RK4Launch& L) {
 }  // namespace
 
 // Three neurons: a lane per neuron (ff_ring.h).  The reset rule and recording
-// treat a particle as a whole and keep one thread per particle, as do
-// ensembles whose lanes would pass the launch limit of 2^32 threads.
+// treat a particle as a whole and keep one thread per particle, as do tunings
+// of two particles per thread and ensembles whose lanes would pass the launch
+// limit of 2^32 threads.
 hipError_t launch_rk4_hh(int neurons, const RK4Launch& L) {
     switch (neurons) {
         case 1: return dispatch_rk4<HH1, 2>(L);
