@@ -107,6 +107,9 @@ ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t ns
     if (plain && sys->rhs == FF_RHS_WILSON_COWAN && prec == FF_FP32_KAHAN && n > 131072 &&
         0.968 * 2.0 * (double)((n + 131071) / 131072) < (double)((n + 65535) / 65536))
         t.particles_per_thread = 2;
+    // A launch holds fewer than 2^32 threads; the runtime takes a larger one
+    // modulo that, and the particles beyond would stay where they are.
+    if (n > ((int64_t)1 << 32) - t.block) t.particles_per_thread = 2;
     return t;
 }
 
