@@ -44,3 +44,39 @@ def test_age_limits(ora, prec, max_age, record):
     assert comp is None or np.array_equal(to_host(comp), want[1])
     assert np.array_equal(to_host(age), want[2])
     assert np.array_equal(to_host(nres).view(np.uint32), want[3])
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp32_kahan", "fp64"])
+@pytest.mark.parametrize("dim", [4, 5, 6])
+def test_each_component_is_tested_against_each_bound(prec, dim):
+    """A state that stays where it is (x' = 0) next to, at and beyond every
+    bound of every component; five single-precision components are tested by
+    other instructions than four and six."""
+    A = api()
+    dtype = torch.float64 if prec == "fp64" else torch.float32
+    ftype = np.float64 if prec == "fp64" else np.float32
+    lo, hi = -1.5 - np.arange(dim) / 3, 0.7 + np.arange(dim) / 7  # not floats
+    cols, out = [], []
+    for d in range(dim):
+        for b in (lo[d], hi[d]):
+            f = ftype(b)
+            for v in (f, np.nextafter(f, ftype(np.inf)), np.nextafter(f, ftype(-np.inf)), ftype(np.inf),
+                      ftype(-np.inf), ftype(np.nan), ftype(-0.0)):
+                x = np.zeros(dim, dtype=ftype)
+                x[d] = v
+                cols.append(x)
+                out.append(not lo[d] <= float(v) <= hi[d])
+    x0 = np.array(cols).T
+    n = x0.shape[1]
+    sys_ = A.System.from_exprs(["0"] * dim, [])
+    x = to_dev(x0, dtype)
+    comp = torch.zeros_like(x) if prec == "fp32_kahan" else None
+    age, nres = (torch.zeros(n, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    A.integrate_reset(sys_, x, 0.01, 1, bounds=list(zip(lo, hi)), box=[(0.1, 0.2)] * dim, age=age, n_resets=nres,
+                      comp=comp, prec=prec)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(nres) == 1, out)
+    assert np.array_equal(to_host(age) == 0, out)
+    keep = ~np.array(out)
+    assert np.array_equal(to_host(x)[:, keep], x0[:, keep])
+    assert np.all((to_host(x)[:, out] >= 0.1) & (to_host(x)[:, out] <= 0.2000001))
