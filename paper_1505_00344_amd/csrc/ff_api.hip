@@ -89,8 +89,18 @@ ff_tuning default_tuning(const ff_system_s* sys, int prec, int64_t n, int64_t ns
     t.steps_per_launch = (int32_t)(nsteps < 4096 ? (nsteps > 0 ? nsteps : 1) : 4096);
     // The three-neuron ring's launches of one or two steps are bound by HBM,
     // which blocks of 128 read a little better (1M, one step, FP64: 106 against
-    // 114 us; FP32: 37.4 against 38.4).
-    t.block = sys->rhs == FF_RHS_HH_RING && sys->dim == 15 && t.steps_per_launch <= 2 ? 128 : 256;
+    // 114 us; FP32: 37.4 against 38.4).  So do the one-neuron ring's of up to
+    // four steps in double precision (checkpoints at every step, per launch:
+    // 300 particles 4.7 against 5.1 us, 524,288 25.0 against 26.2; at every
+    // tenth the same), except where one wave per SIMD holds the ensemble and
+    // more than one block of 128 per CU leaves SIMDs with two (40,000: 7.2
+    // against 5.4).
+    t.block = 256;
+    if (sys->rhs == FF_RHS_HH_RING) {
+        if (sys->dim == 15 ? t.steps_per_launch <= 2
+                           : prec == FF_FP64 && t.steps_per_launch <= 4 && (n <= 32768 || n > 65536))
+            t.block = 128;
+    }
     t.particles_per_thread = 1;
     // Two particles per thread where a sweep on gfx950 found it faster:
     // Wilson-Cowan with the compensated update, whose transcendentals leave
