@@ -216,28 +216,51 @@ struct Prepared {
     bool lanes = true;
 };
 
-// A lane per neuron from eight steps a launch on: below, HBM bounds the ring,
-// and reads its lanes' rows less well.  Between two rounds of lanes and four of
-// threads (43,008 and 262,144 rings) they need as many rounds as threads do
-// and win that back later (60,000 rings, FP32: 8 steps 27.7 -> 31.6 us, 16
-// steps 42.4 -> 44.8, 32 steps 71.2 -> 70.5; 40,000: 25.9 -> 24.5, 39.7 ->
-// 33.3; 300,000: 92.5 -> 89.1, 160 -> 145).  In double precision the lanes gain
-// nothing once one thread per particle fills the chip (500,000 rings in the
-// mixed batch: 12.04 -> 12.24 ms; 100,000: 2.90 -> 2.48).  Without rings the
-// other systems' tiles are faster at the lower occupancy (300,000
-// Wilson-Cowan and 400,000 Lorenz particles, 100 steps, FP32: 120 against 140
-// us).
+// Whether the rings of a batch take a lane per neuron.
+// Steps: below eight a launch HBM bounds the ring, and reads its lanes' rows
+// less well.  Between two rounds of lanes and four of threads (43,008 and
+// 262,144 rings) the steps win that back later (60,000 rings, FP32: 8 steps
+// 27.7 -> 31.6 us, 16 steps 42.4 -> 44.8, 32 steps 71.2 -> 70.5; 40,000: 25.9 ->
+// 24.5, 39.7 -> 33.3; 300,000: 92.5 -> 89.1, 160 -> 145), and so they do in single
+// precision among many particles of other systems, whose tiles are faster at
+// the lower occupancy (5,000 rings, 300,000 Wilson-Cowan and 400,000 Lorenz
+// particles, FP32-Kahan: 8 steps 50 -> 55 us, 16 steps 54 -> 58, 32 steps 77 -> 65;
+// the two without rings, 100 steps, FP32: 120 against 140 us).
+// Rounds: tiles take whole rounds of the CUs, 65,536 rings with a thread each
+// and 21,504 with three lanes each, which cost 0.30 of the former in single
+// precision and 0.337 in double; lanes where they cost less (100 steps, FP32:
+// 65,536 rings 157 -> 190 us, 60,000 188 -> 176, 131,000 1.04 times, 150,000 0.73
+// times; FP64: 260,000 2045 -> 2168, 200,000 1990 -> 1682).  Other systems'
+// tiles can push the threads, not the lanes, into one more round, measured
+// where they have one (60,000 rings and 10,000 others: FP32-Kahan 372 -> 187
+// us, FP64 1025 -> 558) and in plain FP32 (131,000: 536 -> 383).  In double
+// precision the lanes gain nothing once one thread per particle fills the chip
+// (500,000 rings in the mixed batch: 12.04 -> 12.24 ms) or the other systems
+// fill it for as long as one ring takes (21,000 rings, 700,000 Wilson-Cowan and
+// 600,000 Lorenz particles, 100 steps: 714 -> 781 us; 300,000 and 400,000: 561 ->
+// 538).
 bool ring_lanes(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t) {
+    constexpr int64_t kThreads = 65536, kLanes = 21504;  // rings of a round
     if (t.particles_per_thread > 1) return false;  // the caller's tuning, or ff_autotune's, asks for more
     const int64_t steps = std::min<int64_t>(nsteps, t.steps_per_launch);
-    int64_t rings = 0;
-    bool f64 = false;
+    int64_t rings = 0, others = 0;
+    double work = 0.0;  // of the others, per step
+    int prec = FF_FP64;
     for (int i = 0; i < n_groups; ++i) {
-        if (kind_of(groups[i].sys) == K_HH3) rings += groups[i].b.n;
-        f64 = f64 || groups[i].b.prec == FF_FP64;
+        if (groups[i].dt_signed == 0.0) continue;  // paused: no tiles
+        const int kind = kind_of(groups[i].sys);
+        (kind == K_HH3 ? rings : others) += groups[i].b.n;
+        if (kind != K_HH3) work += cost_of(kind) * (double)groups[i].b.n;
+        prec = groups[i].b.prec;
     }
-    if (rings == 0 || (f64 && rings >= 4 * 65536)) return false;
-    return steps >= (rings > 2 * 21504 && rings <= 4 * 65536 ? 32 : 8);
+    if (rings == 0) return false;
+    if (prec == FF_FP64 && (rings >= 4 * kThreads || work >= cost_of(K_HH3) * (double)kThreads)) return false;
+    int64_t threads = (rings + kThreads - 1) / kThreads;
+    const int64_t lanes = (rings + kLanes - 1) / kLanes;
+    if ((threads == 1 || prec == FF_FP32) && rings + others > threads * kThreads) ++threads;
+    if ((prec == FF_FP64 ? 0.337 : 0.30) * (double)lanes >= (double)threads) return false;
+    const bool late = (rings > 2 * kLanes && rings <= 4 * kThreads) || (prec != FF_FP64 && others > 4 * kThreads);
+    return steps >= (late ? 32 : 8);
 }
 
 ff_status prepare(const ff_group* groups, int32_t n_groups, int64_t nsteps, const ff_tuning& t, Prepared* out) {
