@@ -627,10 +627,13 @@ __device__ __forceinline__ uint32_t tile_total(const RSegments<P>& g, int nt, in
     return *s_sum;
 }
 
-// A part of an over-full tile.
+// A part of an over-full tile, in four bytes: an image of few tiles leaves
+// little more in the caller's workspace beside eight bytes per point.  A tile
+// has at most n / per + 1 parts: 411 of points, 822 of sprites (rlayout).
 struct RItem {
-    int32_t tile, part, parts;
+    uint32_t tile : 12, part : 10, parts : 10;
 };
+static_assert(sizeof(RItem) == 4 && kRMaxTiles <= 1 << 12, "the fields of a part");
 
 // The culled particles of all segments, by one block.
 template <int P>
@@ -656,7 +659,7 @@ __device__ __forceinline__ void list_parts(int t, uint32_t total, uint32_t per, 
     __syncthreads();  // s_at may still be read
     if (threadIdx.x == 0) *s_at = atomicAdd(n_items, parts);
     __syncthreads();
-    for (uint32_t k = threadIdx.x; k < parts; k += blockDim.x) items[*s_at + k] = {t, (int32_t)k, (int32_t)parts};
+    for (uint32_t k = threadIdx.x; k < parts; k += blockDim.x) items[*s_at + k] = {(uint32_t)t, k, parts};
 }
 
 // Hand every image value of an LDS tile with a margin of m pixels to
@@ -708,13 +711,14 @@ __global__ void __launch_bounds__(kRSort) k_points_split(RSegments<P> g, RTiles 
     const uint32_t m = *n_items;
     for (uint32_t k = blockIdx.x; k < m; k += gridDim.x) {  // uniform over the block
         const RItem it = items[k];
+        const int tile = (int)it.tile;
         const int b0 = (int)((int64_t)g.nblk * it.part / it.parts);
         const int b1 = (int)((int64_t)g.nblk * (it.part + 1) / it.parts);
         for (int j = threadIdx.x; j < kRTilePx * 3; j += kRSort) s[j] = 0u;
         __syncthreads();
-        gather_runs<P>(s, g, T.nt, it.tile, b0, b1, (uint32_t)it.parts * per);
+        gather_runs<P>(s, g, T.nt, tile, b0, b1, it.parts * per);
         __syncthreads();
-        each_pixel(s, T, it.tile, 0, r, [](uint32_t* d, uint32_t v) { if (v) atomicAdd(d, v); });
+        each_pixel(s, T, tile, 0, r, [](uint32_t* d, uint32_t v) { if (v) atomicAdd(d, v); });
         __syncthreads();
     }
 }
@@ -761,8 +765,8 @@ __global__ void __launch_bounds__(kRSprite, 6) k_sprites_draw(RSegments<P> g, RT
     for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {  // uniform over the block
         const RItem it = items[k];
         // every part but the last is whole; the last ends with the entries
-        sprite_tile<R, P>(lds, wsum, g, T, it.tile, per * (uint32_t)it.part, per * (uint32_t)(it.part + 1), pa, r);
-        each_pixel((const uint32_t*)(lds + sizeof(SpriteList)), T, it.tile, m, r,
+        sprite_tile<R, P>(lds, wsum, g, T, (int)it.tile, per * it.part, per * (it.part + 1), pa, r);
+        each_pixel((const uint32_t*)(lds + sizeof(SpriteList)), T, (int)it.tile, m, r,
                    [](uint32_t* d, uint32_t v) { if (v) atomicAdd(d, v); });
         __syncthreads();
     }
@@ -792,36 +796,39 @@ RLayout rlayout(int64_t n, int width, int height, int radius, double weight, boo
     L.total = align256((size_t)n * 4) + align256((size_t)L.ntiles * (size_t)chunks * 4) +
               align256((size_t)L.ntiles * 4) + 2 * align256((size_t)(L.ntiles + 1) * 4) +
               align256((size_t)(radius == 0 ? n : 4 * n) * 4);
-    auto lay_out = [&](int payload) {
+    auto lay_out = [&](int payload, int K) {
         L.payload = payload;
-        // particles per thread: one block for each of the 256 CUs while the
-        // ensemble is too small to fill them otherwise, and few segments
-        // (short columns of starts) beyond; bounded by the LDS that sorts them
-        const int64_t full = 256 * (int64_t)kRSort;
-        if (payload == kPack32) L.K = n <= full ? 1 : n <= 4 * full ? 4 : 8;
-        else L.K = payload != kPack64 && n <= full && L.ntiles <= 2048 ? 1 : 4;
+        L.K = K;
         const int64_t C = (int64_t)kRSort * L.K;
         L.nblk = (int)((n + C - 1) / C);
         // an evenly filled tile stays whole; sprites cost enough to be split finely
-        L.per = (uint32_t)(payload >= kCoords ? std::max<int64_t>(768, 5 * n / 4096)
-                                              : std::max<int64_t>(8192, 5 * n / 2048));
+        const int64_t least = payload >= kCoords ? 768 : payload == kPack64 && K == 8 ? 12288 : 8192;
+        L.per = (uint32_t)std::max<int64_t>(least, 5 * n / (payload >= kCoords ? 4096 : 2048));
         const int size = payload == kCoords ? 12 : payload == kPack64 ? 8 : 4;
         L.sorted = 0;
         L.starts = align256((size_t)n * size);
-        L.items = L.starts + align256((size_t)L.nblk * (L.ntiles + 2) * 2);
-        const int64_t parts =  // at most
-            payload >= kCoords ? std::min<int64_t>(n, n / L.per + L.ntiles) : n > L.per ? 2 * n / L.per : 0;
-        L.n_items = L.items + align256((size_t)parts * sizeof(RItem));
-        return L.n_items + 256 + 16 <= L.total;  // 16: room to align the buffers
+        L.items = L.starts + ((size_t)L.nblk * (L.ntiles + 2) * 2 + 3) / 4 * 4;
+        // at most: each of the listed tiles, of points those over-full, one more
+        // than its share of n / per
+        const int64_t whole = n / L.per;
+        const int64_t parts =
+            payload >= kCoords ? std::min<int64_t>(n, whole + L.ntiles) : whole + std::min<int64_t>(whole, L.ntiles);
+        L.n_items = L.items + (size_t)parts * sizeof(RItem);
+        return L.n_items + 4 + 16 <= L.total;  // 16: room to align the buffers
     };
-    // A point's largest colour value is that of rgb = 1.  Eight bytes per
-    // point can pass the size above on images of a few tiles; the other
-    // payloads never do (the direct path draws the smallest ensembles).
+    // Particles per thread: one block for each of the 256 CUs while the ensemble
+    // is too small to fill them otherwise, and few segments (short columns of
+    // starts) beyond; bounded by the LDS that sorts them.  Points of eight bytes
+    // take twice as many where the starts of more segments would pass the size
+    // above, on images of one or two tiles.  A point's largest colour value is
+    // that of rgb = 1.
+    const int64_t full = 256 * (int64_t)kRSort;
     const double top = std::rint(256.0 * weight);
-    if (radius == 0 && top <= 127.0 && lay_out(kPack32)) return L;
-    if (radius == 0 && top <= 131071.0 && lay_out(kPack64)) return L;
-    if (radius > 0 && !f64 && lay_out(kCoords)) return L;
-    (void)lay_out(kIndex);
+    const int few = n <= full && L.ntiles <= 2048 ? 1 : 4;
+    if (radius == 0 && top <= 127.0 && lay_out(kPack32, n <= full ? 1 : n <= 4 * full ? 4 : 8)) return L;
+    if (radius == 0 && top <= 131071.0 && (lay_out(kPack64, 4) || lay_out(kPack64, 8))) return L;
+    if (radius > 0 && !f64 && lay_out(kCoords, few)) return L;
+    (void)lay_out(kIndex, few);
     return L;
 }
 
@@ -848,7 +855,7 @@ hipError_t partition(const R* a0, const R* a1, const R* a2, int64_t n, const Ren
     else if (L.K == 4)
         hipLaunchKernelGGL((k_render_partition<R, 4, P>), grid, block, 0, to.st, a0, a1, a2, n, r, L.ntx, L.ntiles,
                            sorted, starts, n_items, to.img, clear);
-    else if constexpr (P == kPack32)
+    else if constexpr (P == kPack32 || P == kPack64)
         hipLaunchKernelGGL((k_render_partition<R, 8, P>), grid, block, 0, to.st, a0, a1, a2, n, r, L.ntx, L.ntiles,
                            sorted, starts, n_items, to.img, clear);
     return hipGetLastError();
