@@ -77,7 +77,7 @@ constexpr int kRSort = 1024;                      // threads of a partition bloc
 constexpr int64_t kRChunk = 4096;
 constexpr int64_t kRMaxCounts = (int64_t)1 << 26;  // tiles x chunks of the tiled path
 constexpr int64_t kRDirectMax = 8192;              // points drawn by the direct path
-constexpr int kRList = 512;                        // sprites an accumulate block holds at a time
+constexpr int kRList = 512;                        // sprites a draw block holds at a time
 constexpr int kRSprite = 512;                      // threads of such a block
 constexpr int64_t kRMaxN = (int64_t)1 << 29;       // 4 n entries stay below 2^31 (uint32 offsets)
 constexpr uint32_t kRNone = 0xFFFFFFFFu;
@@ -432,7 +432,7 @@ __device__ __forceinline__ void gather_points(uint32_t* s, const RSegments<P>& g
 // threads a run or, where that takes more rounds of loads, by the whole block:
 // few segments (a small ensemble) or an ensemble in few tiles leave few, long
 // runs.  9,000 points of weight 1 on a 64 x 48 image (3 runs of 1500 a tile):
-// 57 -> 22 us; 200,003 on a line of a 200 x 100 image: 43 -> 26.
+// 57 -> 24 us; 200,003 on a line of a 200 x 100 image: 43 -> 27.
 template <int P>
 __device__ __forceinline__ void gather_runs(uint32_t* s, const RSegments<P>& g, int nt, int t, int b0, int b1,
                                             uint32_t total) {
@@ -448,11 +448,18 @@ __device__ __forceinline__ void gather_runs(uint32_t* s, const RSegments<P>& g, 
 // first joins the runs into a list, then projects the list's particles, one a
 // thread, into these records, and last draws row by row, one row of one
 // sprite a thread, so that every lane has work whatever the runs.
-struct SpriteList {
-    uint32_t entry[kRList];          // position in the segments
-    uint32_t box[kRList];            // first column (7 bits) and row (6) in the tile, from bit 16 columns and rows less one (5 each)
-    float dx0[kRList], dy0[kRList];  // centre of the first pixel less the sprite's
-    float A[3][kRList];              // 256 weight rgb
+// EXACT: the records and the rows in double precision, half as many at a time.
+template <bool EXACT> struct SpriteList {
+    static constexpr int kN = kRList;
+    uint32_t entry[kN];      // position in the segments
+    uint32_t box[kN];        // first column (7 bits) and row (6) in the tile, from bit 16 columns and rows less one (5 each)
+    float dx0[kN], dy0[kN];  // centre of the first pixel less the sprite's
+    float A[3][kN];          // 256 weight rgb
+};
+template <> struct SpriteList<true> {
+    static constexpr int kN = kRList / 2;
+    uint32_t entry[kN], box[kN];
+    double px[kN], py[kN], rgb[3][kN];  // the sprite's centre and colour
 };
 constexpr uint32_t kNoRows = 31;  // a sprite has at most 2 (R + 1) = 18 rows
 
@@ -476,8 +483,9 @@ template <typename R, int P> struct Particles {
 // A listed particle's record.  Its box holds the image's pixels whose centres
 // are nearer than the sprite's reach in either direction (no other can be in
 // the disc).
-__device__ __forceinline__ void sprite_record(const Point& P, const RenderArgs& r, int X0, int Y0, SpriteList& L,
-                                              uint32_t j) {
+template <bool EXACT>
+__device__ __forceinline__ void sprite_record(const Point& P, const RenderArgs& r, int X0, int Y0,
+                                              SpriteList<EXACT>& L, uint32_t j) {
     int x0, x1, y0, y1;
     sprite_box(P, r.radius, x0, x1, y0, y1);
     if (r.radius > 0) {
@@ -494,10 +502,17 @@ __device__ __forceinline__ void sprite_record(const Point& P, const RenderArgs& 
     L.box[j] = x0 > x1 || y0 > y1 ? kNoRows << 21
                                   : (uint32_t)(x0 - X0) | (uint32_t)(y0 - Y0) << 7 | (uint32_t)(x1 - x0) << 16 |
                                         (uint32_t)(y1 - y0) << 21;
-    L.dx0[j] = (float)(((double)x0 + 0.5) - P.px);
-    L.dy0[j] = (float)(((double)y0 + 0.5) - P.py);
+    if constexpr (EXACT) {
+        L.px[j] = P.px;
+        L.py[j] = P.py;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) L.A[k][j] = (float)(256.0 * (r.weight * P.rgb[k]));
+        for (int k = 0; k < 3; ++k) L.rgb[k][j] = P.rgb[k];
+    } else {
+        L.dx0[j] = (float)(((double)x0 + 0.5) - P.px);
+        L.dy0[j] = (float)(((double)y0 + 0.5) - P.py);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) L.A[k][j] = (float)(256.0 * (r.weight * P.rgb[k]));
+    }
 }
 
 // Row `row` of record j's sprite into the LDS tile (`pitch` values a row).
@@ -508,7 +523,7 @@ __device__ __forceinline__ void sprite_record(const Point& P, const RenderArgs& 
 // the products 26 u), and again in double precision where that could change
 // the rounding.
 template <typename R, int P>
-__device__ __forceinline__ void sprite_row(const SpriteList& L, uint32_t j, uint32_t row, const RenderArgs& r,
+__device__ __forceinline__ void sprite_row(const SpriteList<false>& L, uint32_t j, uint32_t row, const RenderArgs& r,
                                            int X0, int Y0, uint32_t* s, int pitch, const Particles<R, P>& pa) {
     const uint32_t box = L.box[j], rows = box >> 21;
     if (row > rows || rows == kNoRows) return;
@@ -544,12 +559,33 @@ __device__ __forceinline__ void sprite_row(const SpriteList& L, uint32_t j, uint
     }
 }
 
+// The same by the double-precision operations alone.
+template <typename R, int P>
+__device__ __forceinline__ void sprite_row(const SpriteList<true>& L, uint32_t j, uint32_t row, const RenderArgs& r,
+                                           int X0, int Y0, uint32_t* s, int pitch, const Particles<R, P>&) {
+    const uint32_t box = L.box[j], rows = box >> 21;
+    if (row > rows || rows == kNoRows) return;
+    const int bx = (int)(box & 127u), by = (int)((box >> 7) & 63u), nx = (int)((box >> 16) & 31u);
+    const Point pt{true, L.px[j], L.py[j], {L.rgb[0][j], L.rgb[1][j], L.rgb[2][j]}};
+    uint32_t* px = s + (by + (int)row) * pitch + 3 * bx;
+    for (int ix = 0; ix <= nx; ++ix, px += 3) {
+        double w;
+        if (!pixel_weight(pt, X0 + bx + ix, Y0 + by + (int)row, r, w)) continue;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t v = quantise(w, pt.rgb[k]);
+            if (v) atomicAdd(px + k, v);
+        }
+    }
+}
+
 // Tile t's sprites number e0 .. e1 - 1 (counted over all segments), added to
 // the LDS tile.
-template <typename R, int P>
-__device__ __forceinline__ void gather_sprites(uint32_t* s, SpriteList& L, uint32_t* wsum, const RSegments<P>& g,
+template <typename R, int P, bool EXACT>
+__device__ __forceinline__ void gather_sprites(uint32_t* s, SpriteList<EXACT>& L, uint32_t* wsum, const RSegments<P>& g,
                                                int ntx, int nt, int t, uint32_t e0, uint32_t e1,
                                                const Particles<R, P>& pa, const RenderArgs& r) {
+    constexpr uint32_t kList = SpriteList<EXACT>::kN;
     const int X0 = (t % ntx) * kRTileW, Y0 = (t / ntx) * kRTileH;
     const int tid = threadIdx.x;
     const uint32_t margin = r.radius > 0 ? 2u * (uint32_t)(r.radius + 1) : 0u, rows = margin ? margin : 1u;
@@ -558,7 +594,7 @@ __device__ __forceinline__ void gather_sprites(uint32_t* s, SpriteList& L, uint3
     uint32_t held = 0;  // entries in the list, uniform over the block
     auto draw = [&]() {
         __syncthreads();
-        for (uint32_t j = tid; j < held; j += kRSprite) sprite_record(pa.at(L.entry[j], r), r, X0, Y0, L, j);
+        for (uint32_t j = tid; j < held; j += kRSprite) sprite_record<EXACT>(pa.at(L.entry[j], r), r, X0, Y0, L, j);
         __syncthreads();
         for (uint32_t w = tid; w < held * rows; w += kRSprite) {
             // w / rows: w is below 2^14, so the product is off by far less
@@ -589,7 +625,7 @@ __device__ __forceinline__ void gather_sprites(uint32_t* s, SpriteList& L, uint3
         lo += from - off;
         off = from - s0;
         for (uint32_t done = 0; done < all;) {
-            const uint32_t take = all - done < kRList - held ? all - done : kRList - held;
+            const uint32_t take = all - done < kList - held ? all - done : kList - held;
             // the entries at positions done .. done + take - 1: each thread
             // lists its short run, a wave its long ones together
             if (__ballot(len > 32) == 0) {
@@ -605,7 +641,7 @@ __device__ __forceinline__ void gather_sprites(uint32_t* s, SpriteList& L, uint3
             }
             held += take;
             done += take;
-            if (held == kRList) draw();
+            if (held == kList) draw();
         }
     }
     if (held) draw();
@@ -724,19 +760,19 @@ __global__ void __launch_bounds__(kRSort) k_points_split(RSegments<P> g, RTiles 
 }
 
 // LDS of a sprite block: the list, then the tile with its margins.
-size_t sprite_lds(int radius) {
+template <bool EXACT> size_t sprite_lds(int radius) {
     const size_t m = radius > 0 ? 2 * (size_t)(radius + 1) : 0;
-    return sizeof(SpriteList) + (kRTileW + m) * (kRTileH + m) * 12;
+    return sizeof(SpriteList<EXACT>) + (kRTileW + m) * (kRTileH + m) * 12;
 }
 
-template <typename R, int P>
+template <typename R, int P, bool EXACT>
 __device__ __forceinline__ void sprite_tile(char* lds, uint32_t* wsum, const RSegments<P>& g, const RTiles& T, int t,
                                             uint32_t e0, uint32_t e1, const Particles<R, P>& pa, const RenderArgs& r) {
     const int m = r.radius > 0 ? 2 * (r.radius + 1) : 0;
-    uint32_t* s = (uint32_t*)(lds + sizeof(SpriteList));
+    uint32_t* s = (uint32_t*)(lds + sizeof(SpriteList<EXACT>));
     for (int k = threadIdx.x; k < 3 * (kRTileW + m) * (kRTileH + m); k += kRSprite) s[k] = 0u;
     __syncthreads();
-    gather_sprites<R, P>(s, *(SpriteList*)lds, wsum, g, T.ntx, T.nt, t, e0, e1, pa, r);
+    gather_sprites<R, P, EXACT>(s, *(SpriteList<EXACT>*)lds, wsum, g, T.ntx, T.nt, t, e0, e1, pa, r);
     __syncthreads();
 }
 
@@ -754,7 +790,7 @@ __global__ void __launch_bounds__(256) k_sprites_list(RSegments<P> g, RTiles T, 
 // 3. the listed parts, sprites.  Six waves per SIMD, three blocks of a CU's LDS
 // (radius 2): at the 88 VGPRs it takes otherwise two fit (61 -> 69 us for
 // 500,009 sprites).
-template <typename R, int P>
+template <typename R, int P, bool EXACT>
 __global__ void __launch_bounds__(kRSprite, 6) k_sprites_draw(RSegments<P> g, RTiles T, uint32_t per,
                                                               Particles<R, P> pa, RenderArgs r, const RItem* items,
                                                               const uint32_t* n_items) {
@@ -765,12 +801,20 @@ __global__ void __launch_bounds__(kRSprite, 6) k_sprites_draw(RSegments<P> g, RT
     for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {  // uniform over the block
         const RItem it = items[k];
         // every part but the last is whole; the last ends with the entries
-        sprite_tile<R, P>(lds, wsum, g, T, (int)it.tile, per * it.part, per * (it.part + 1), pa, r);
-        each_pixel((const uint32_t*)(lds + sizeof(SpriteList)), T, (int)it.tile, m, r,
+        sprite_tile<R, P, EXACT>(lds, wsum, g, T, (int)it.tile, per * it.part, per * (it.part + 1), pa, r);
+        each_pixel((const uint32_t*)(lds + sizeof(SpriteList<EXACT>)), T, (int)it.tile, m, r,
                    [](uint32_t* d, uint32_t v) { if (v) atomicAdd(d, v); });
         __syncthreads();
     }
 }
+
+// Heavy sprites are drawn in double precision throughout (EXACT): in single
+// precision many of their values are in doubt, and a wave takes the
+// double-precision way, which projects the particle again, for any of its lanes
+// (1M sprites of radius 4 in 1920 x 1080, single precision against this: weight 1
+// 182 to 312 us, 8 319 to 308, 40 563 to 312; radius 1: weight 1 96 to 129, 12 126
+// to 129, 20 138 to 128).
+bool exact_sprites(const RenderArgs& r) { return r.weight > (r.radius > 1 ? 8.0 : 16.0); }
 
 struct RLayout {
     bool tiled;      // the call uses scratch (and asks for `total` bytes of it)
@@ -876,8 +920,12 @@ hipError_t run_tiles(const R* a0, const R* a1, const R* a2, int64_t n, const Ren
                            n_items);
         if (hipError_t e = hipGetLastError()) return e;
         const unsigned grid = (unsigned)std::min<int64_t>(1024, n / L.per + L.ntiles);
-        hipLaunchKernelGGL((k_sprites_draw<R, P>), dim3(grid), dim3(kRSprite), sprite_lds(r.radius), to.st, g, T, L.per, pa,
-                           r, items, n_items);
+        if (exact_sprites(r))
+            hipLaunchKernelGGL((k_sprites_draw<R, P, true>), dim3(grid), dim3(kRSprite), sprite_lds<true>(r.radius),
+                               to.st, g, T, L.per, pa, r, items, n_items);
+        else
+            hipLaunchKernelGGL((k_sprites_draw<R, P, false>), dim3(grid), dim3(kRSprite), sprite_lds<false>(r.radius),
+                               to.st, g, T, L.per, pa, r, items, n_items);
     } else {
         hipLaunchKernelGGL((k_points_accum<P>), dim3(L.ntiles + 1), dim3(kRSort), 0, to.st, g, T, L.per, r, to.culled,
                            items, n_items);

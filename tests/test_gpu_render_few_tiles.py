@@ -36,3 +36,22 @@ def test_points(ora, n, size, kind):
         assert np.array_equal(to_host(img).view(np.uint32), want)
         assert int(cu.item()) == wc
         assert bool((buf[:guard] == 165).all()) and bool((buf[guard + need:] == 165).all())
+
+
+@pytest.mark.parametrize("radius", [1, 2, 5, 8])
+@pytest.mark.parametrize("weight", [7.99, 8.01, 15.99, 16.01, 900.0])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_heavy_sprites(ora, radius, weight, dtype):
+    """Both sides of the weights from which sprites are drawn in double precision throughout."""
+    A = api()
+    n, size = 3001, (150, 70)
+    rng = np.random.default_rng(n)
+    x = rng.uniform(-1.05, 1.05, (3, n))
+    x[:2, ::2] = np.round(x[:2, ::2] * 64) / 64  # centres on pixel corners: many equal distances
+    x[0, ::97] = np.nan
+    st = to_dev(x, dtype)
+    kw = dict(base=(0.2, 0.5, 1.0), grad=[[0.3, 0, 0], [0, 0.4, 0], [0, 0, -0.5]], weight=weight, radius=radius)
+    img, cu = A.render_image(A.System("lorenz", 3, I.LORENZ_PARAMS), st, (0, 1, 2), MVP, *size, **kw)
+    want, wc = ora.render(to_host(st).astype(np.float64), ora.render_spec((0, 1, 2), MVP, *size, **kw))
+    assert np.array_equal(to_host(img).view(np.uint32), want)
+    assert int(cu.item()) == wc
