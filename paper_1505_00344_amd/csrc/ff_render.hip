@@ -813,8 +813,8 @@ __global__ void __launch_bounds__(kRSprite, 6) k_sprites_draw(RSegments<P> g, RT
 // double-precision way, which projects the particle again, for any of its lanes
 // (1M sprites of radius 4 in 1920 x 1080, single precision against this: weight 1
 // 182 to 312 us, 8 319 to 308, 40 563 to 312; radius 1: weight 1 96 to 129, 12 126
-// to 129, 20 138 to 128).
-bool exact_sprites(const RenderArgs& r) { return r.weight > (r.radius > 1 ? 8.0 : 16.0); }
+// to 129, 20 138 to 128; points by index, weight 600: 8M 581 to 835).
+bool exact_sprites(const RenderArgs& r) { return r.radius > 0 && r.weight > (r.radius > 1 ? 8.0 : 16.0); }
 
 struct RLayout {
     bool tiled;      // the call uses scratch (and asks for `total` bytes of it)
