@@ -21,10 +21,12 @@
 
 namespace ff {
 
-// The 15-variable ring (and expression systems of more than four variables)
-// keep one step on the tape and recompute stage points (LOWREG); the small
-// systems keep eight, Lorenz in double precision four (it also keeps every
-// tape state's stage points; the launcher in k_adj_lorenz.hip must agree).
+// The rings and expression systems of more than four variables keep one step on
+// the tape.  The one-neuron ring and those expression systems also park its
+// stage points in LDS (LOWREG); the three-neuron ring, with a lane per neuron,
+// holds them in registers.  The small systems keep eight steps, Lorenz in double
+// precision four (it also keeps every tape state's stage points; the launcher in
+// k_adj_lorenz.hip must agree).
 int adj_tape_len(const ff_system_s* sys, int prec) {
     if (sys->rhs == FF_RHS_HH_RING) return 1;
     if (sys->rhs == FF_RHS_EXPR) return sys->dim <= 4 ? 8 : 1;

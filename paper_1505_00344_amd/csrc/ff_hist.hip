@@ -16,7 +16,8 @@
 //      `sorted`, with the start of every tile in it; it also clears its share
 //      of the grid
 //   2. accumulate: one block owns a tile, gathers the tile's runs from all
-//      segments into an LDS histogram and stores its non-zero bins.  A tile
+//      segments into an LDS histogram and stores its non-zero bins (or adds
+//      them, atomically, to an accumulated grid).  A tile
 //      that holds more than a block's share of the particles is listed instead
 //      and split over blocks of a third launch, which add theirs with atomics.
 // Square tiles keep an attractor, a curve on the grid, spread over many
@@ -26,8 +27,9 @@
 // (partition 33, accumulate 15, split 13), of which reading the coordinates at
 // the 4.6 TB/s of a large copy is 15; a counting sort over the whole grid
 // (count, two scans, scatter, accumulate in chunks of 8192 merged by atomics)
-// took the 146.  The partition is bound by the LDS counting of a skewed
-// ensemble (23 us when uniform), the others by the latency of short loads.
+// took the 146.  All three wait (69-75 % of their waves' time): the partition
+// for the LDS atomics that return a particle's rank, which take turns in a
+// skewed ensemble's tiles (23 us when uniform), the others for short loads.
 // Ensembles of at most kDirectMax particles add straight to the grid with
 // global atomics, and grids of at most 16384 bins use one LDS histogram per
 // block over a stride of particles.

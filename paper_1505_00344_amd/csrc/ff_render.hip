@@ -42,12 +42,14 @@
 // image once.  8,388,608 settled Lorenz particles at 1920 x 1080: 410 -> 99 us
 // (partition 55, points 25, their parts 21), of which reading the coordinates
 // and writing the image at the 4.6 TB/s of a large copy are 27; the partition
-// is bound by its double-precision projection and the LDS counting.  500,009
-// sprites of radius 2 at 1280 x 720: 137 -> 60 us (partition 12, list 5, draw
-// 43), bound by VALU issue on 36 pixels a sprite.  Before, a counting sort over
-// the whole image held particle indices: gathering their coordinates read a
-// line of memory for each, every chunk of 1024 entries merged its tile by
-// atomics, and every pixel took a double-precision square root and division.
+// is bound by VALU issue (70 %), near half of it the double-precision
+// projection, the others wait for short gathers (62-71 % of their waves' time).
+// 500,009 sprites of radius 2 at 1280 x 720: 137 -> 60 us (partition 12, list
+// 5, draw 43); the draw waits two thirds of its waves' time, at barriers and
+// for LDS, with VALU issue at 57 % and the LDS at 24 %.  Before, a counting
+// sort over the whole image held particle indices: gathering their coordinates
+// read a line of memory for each, every chunk of 1024 entries merged its tile
+// by atomics, and every pixel took a double-precision square root and division.
 // Larger sprites or images, and few points, use the direct path: one thread
 // per particle, global atomics per pixel.
 #include <algorithm>
